@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(HERE, "_lib")
 LIB = os.path.join(OUT_DIR, "liblbib.so")
 SOURCES = ["lbib_sweep.hip", "lbib_pool_sweep.hip", "lbib_particle.hip", "lbib_runtime.cpp", "lbib_pool.cpp",
-           "lbib_serve.cpp", "lbib_host.cpp", "lbib_geometry.cpp", "lbib_static.hip"]
+           "lbib_serve.cpp", "lbib_host.cpp", "lbib_geometry.cpp", "lbib_static.hip",
+           "lbib_fields.hip"]
 ARCH = "gfx950"
 
 FLAGS = [
@@ -28,7 +29,8 @@ FLAGS = [
 # simulation gives bit-identical results whichever kernel variant runs it (one simulation
 # or a pool, push or pull layout, any number of markers per thread).  The host file is built
 # the same way: its equilibrium, used by read-outs of the f - f_eq storages, matches the device's.
-PER_SOURCE = {src: ["-ffp-contract=off"] for src in ("lbib_sweep.hip", "lbib_pool_sweep.hip", "lbib_particle.hip", "lbib_host.cpp")}
+PER_SOURCE = {src: ["-ffp-contract=off"] for src in ("lbib_sweep.hip", "lbib_pool_sweep.hip", "lbib_particle.hip", "lbib_fields.hip",
+                                                        "lbib_host.cpp")}
 
 
 def hipcc() -> str:

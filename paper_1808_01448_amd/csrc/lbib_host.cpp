@@ -53,37 +53,12 @@ uint16_t f32_to_f16(float f)
     return (uint16_t)(sign | r);
 }
 
-float f16_to_f32(uint16_t h)
-{
-    const uint32_t sign = (uint32_t)(h & 0x8000u) << 16, e = (h >> 10) & 0x1fu, m = h & 0x3ffu;
-    uint32_t x;
-    if (e == 0) {
-        const float v = std::ldexp((float)m, -24);  // zero or subnormal, exact
-        return sign ? -v : v;
-    }
-    if (e == 31)
-        x = sign | 0x7f800000u | (m << 13);
-    else
-        x = sign | ((e + 112u) << 23) | (m << 13);
-    float f;
-    std::memcpy(&f, &x, 4);
-    return f;
-}
-
 uint16_t f32_to_bf16(float f)
 {
     uint32_t x;
     std::memcpy(&x, &f, 4);
     x = (x & 0x7fffffffu) > 0x7f800000u ? 0x7fc00000u : x + 0x7fffu + ((x >> 16) & 1u);
     return (uint16_t)(x >> 16);
-}
-
-float bf16_to_f32(uint16_t h)
-{
-    const uint32_t x = (uint32_t)h << 16;
-    float f;
-    std::memcpy(&f, &x, 4);
-    return f;
 }
 
 int64_t host_pop_index(const LatticeGeom& g, int q, int i, int j)
@@ -487,34 +462,6 @@ static double neq_term(const LatticeGeom& g, const float* m, int q, int i, int j
     return feq_shift_host(dir, (double)m[c], (double)m[g.plane + c], (double)m[2 * g.plane + c]);
 }
 
-hipError_t download_populations(const void* fdev, const LatticeGeom& g, std::vector<double>& f)
-{
-    const int nx = g.nx, ny = g.ny;
-    f.assign((size_t)9 * nx * ny, 0.0);
-    std::vector<unsigned char> raw(g.buf_bytes);
-    hipError_t e = hipMemcpy(raw.data(), fdev, raw.size(), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return e;
-    const float* mom = (const float*)(raw.data() + (size_t)9 * g.row * ny * g.elem);
-    const double inv = 1.0 / g.scale;
-    for (int q = 0; q < 9; ++q)
-        for (int j = 0; j < ny; ++j)
-            for (int i = 0; i < nx; ++i) {
-                const int64_t k = host_pop_index(g, q, i, j);
-                double v = 0.0;
-                switch (g.precision) {
-                    case LBIB_FP64: v = ((const double*)raw.data())[k]; break;
-                    case LBIB_FP32: v = (double)((const float*)raw.data())[k]; break;
-                    case LBIB_FP16:
-                    case LBIB_FP16_NEQ: v = (double)f16_to_f32(((const uint16_t*)raw.data())[k]) * inv; break;
-                    default: v = (double)bf16_to_f32(((const uint16_t*)raw.data())[k]); break;
-                }
-                if (g.neq) v += neq_term(g, mom, q, i, j);
-                if (j == ny - 1) v += wall_term(g, q);
-                f[((size_t)q * ny + j) * nx + i] = kWq[q] + v;
-            }
-    return hipSuccess;
-}
-
 hipError_t upload_populations(void* fdev, const LatticeGeom& g, const double* f)
 {
     const int nx = g.nx, ny = g.ny;
@@ -554,25 +501,6 @@ hipError_t upload_populations(void* fdev, const LatticeGeom& g, const double* f)
                 }
             }
     return hipMemcpy(fdev, raw.data(), raw.size(), hipMemcpyHostToDevice);
-}
-
-void field_from_populations(const std::vector<double>& f, const LatticeGeom& g, int which, double* out)
-{
-    const size_t N = (size_t)g.nx * g.ny;
-    if (which == 3) {
-        std::memcpy(out, f.data(), f.size() * sizeof(double));
-        return;
-    }
-    for (size_t c = 0; c < N; ++c) {
-        double r = 0, jx = 0, jy = 0;
-        for (int q = 0; q < 9; ++q) {
-            const double v = f[q * N + c];
-            r += v;
-            jx += v * kExq[q];
-            jy += v * kEyq[q];
-        }
-        out[c] = which == 0 ? r : which == 1 ? (jx + 0.5 * g.gx) / r : (jy + 0.5 * g.gy) / r;
-    }
 }
 
 }  // namespace lbib

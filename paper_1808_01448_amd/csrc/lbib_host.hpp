@@ -39,9 +39,7 @@ struct LatticeGeom {
 
 // Host conversions of the 16-bit storages (round to nearest even).
 uint16_t f32_to_f16(float f);
-float f16_to_f32(uint16_t h);
 uint16_t f32_to_bf16(float f);
-float bf16_to_f32(uint16_t h);
 
 // Element index of population q of node (i, j) in a buffer of this geometry (the host
 // mirror of the device's pop_index).
@@ -147,11 +145,16 @@ void set_null_error(const std::string& msg);
 // padding zeroed.
 hipError_t init_populations(void* f, const LatticeGeom& g, hipStream_t s);
 
-// Plain FP64 populations [9][ny][nx] from a device buffer of shifted ones.
-hipError_t download_populations(const void* fdev, const LatticeGeom& g, std::vector<double>& f);
+// Device staging of the field read-outs, kept by its simulation or pool: as large as the largest
+// result read, 64 MiB (or one row) at most.
+struct FieldStage {
+    double* p = nullptr;
+    size_t bytes = 0;
+};
+// rho (which 0), u_x (1), u_y (2) or the plain populations [9][ny][nx] (3) of a device buffer,
+// in FP64, to the caller's memory; enqueued on `s` and waited for.
+hipError_t read_field(const void* f, const LatticeGeom& g, int which, double* out, FieldStage& st, hipStream_t s);
 // Overwrite a device buffer with plain FP64 populations [9][ny][nx].
 hipError_t upload_populations(void* fdev, const LatticeGeom& g, const double* f);
-// rho (which 0), u_x (1), u_y (2) or the populations (3) from plain populations.
-void field_from_populations(const std::vector<double>& f, const LatticeGeom& g, int which, double* out);
 
 }  // namespace lbib

@@ -146,6 +146,7 @@ struct lbib_pool {
     int32_t graph_steps = 0;
     hipGraphExec_t graph = nullptr;
     int64_t pool_steps = 0;
+    FieldStage stage;
     // kernel timing: kind 0 sweep, 1 particle phase
     bool timing = false;
     std::vector<hipEvent_t> ev[2];
@@ -612,9 +613,7 @@ lbib_status lbib_pool_read_field(lbib_pool_handle h, int32_t slot, int32_t which
         PCHK(h, hipStreamSynchronize(h->stream));
         DevParticle st;
         PCHK(h, hipMemcpy(&st, m->p.d_st, sizeof(st), hipMemcpyDeviceToHost));
-        std::vector<double> f;
-        PCHK(h, download_populations((st.step & 1) ? m->fB : m->fA, m->g, f));
-        field_from_populations(f, m->g, which, out);
+        PCHK(h, read_field((st.step & 1) ? m->fB : m->fA, m->g, which, out, h->stage, h->stream));
     } catch (const std::bad_alloc&) {
         return fail(h, LBIB_E_NOMEM, "lbib_pool_read_field: host allocation failed");
     }
@@ -835,6 +834,7 @@ void lbib_pool_destroy(lbib_pool_handle h)
     dfree(h->d_active);
     dfree(h->d_table);
     dfree(h->d_ctl);
+    dfree(h->stage.p);
     if (h->graph) (void)hipGraphExecDestroy(h->graph);
     for (int k = 0; k < 2; ++k)
         for (auto e : h->ev[k]) (void)hipEventDestroy(e);

@@ -64,6 +64,7 @@ struct lbib_sim {
     bool h_flags_valid = false;
     hipEvent_t ev_end = nullptr;
     int64_t steps = 0;
+    FieldStage stage;
     Timing timing;
     // split particle phase (several particles, or overlap mode 3): the two tile masks (by
     // step parity), every particle's box and tile, the particle arguments on the device
@@ -151,6 +152,8 @@ void free_all(lbib_sim* h)
     h->h_flags_valid = false;
     if (h->ev_end) (void)hipEventDestroy(h->ev_end);
     h->ev_end = nullptr;
+    dfree(h->stage.p);
+    h->stage.bytes = 0;
     dfree(h->d_masks);
     dfree(h->d_bar);
     dfree(h->d_refs);
@@ -503,13 +506,6 @@ Particle* get_particle(lbib_sim* h, int32_t pid)
     return &h->parts[pid];
 }
 
-// Populations on the device -> plain FP64 f (host, [9][ny][nx]).
-lbib_status download_f(lbib_sim* h, std::vector<double>& f)
-{
-    HIPCHK(h, download_populations(h->fA, h->g, f));
-    return LBIB_OK;
-}
-
 struct BlobHeader {
     char magic[8];
     int32_t version, nx, ny, precision, n_particles, nl;
@@ -791,11 +787,7 @@ lbib_status lbib_read_field(lbib_handle h, int32_t which, double* out, int64_t c
     const int64_t need = (which == 3 ? 9 : 1) * (int64_t)h->desc.nx * h->desc.ny;
     if (capacity < need) return fail(h, LBIB_E_INVALID, "lbib_read_field: capacity must be >= " + std::to_string(need));
     try {
-        HIPCHK(h, hipStreamSynchronize(h->stream));
-        std::vector<double> f;
-        lbib_status s = download_f(h, f);
-        if (s != LBIB_OK) return s;
-        field_from_populations(f, h->g, which, out);
+        HIPCHK(h, read_field(h->fA, h->g, which, out, h->stage, h->stream));
     } catch (const std::bad_alloc&) {
         return fail(h, LBIB_E_NOMEM, "lbib_read_field: host allocation failed");
     }
