@@ -340,8 +340,10 @@ enum { LBIB_POOL_RUNNING = 0, LBIB_POOL_FINISHED = 1, LBIB_POOL_FAILED = 2 };
 /* Create a pool.  precision: LBIB_FP64 or LBIB_FP32 storage for every member;
  * hbm_budget_bytes: device memory the members may occupy together, allocated here in one
  * piece (members are placed in it first fit, so joining and leaving never allocate or free
- * device memory; the pool's own tables come on top: about 8 bytes per 256 lattice nodes and
- * 1 KB per member); max_members in [1, 65536]; hip_stream as for lbib_create. */
+ * device memory; the pool's own tables come on top: about 16 bytes per 256 lattice nodes and
+ * 1 KB per member, for large pools a second spread-force tile per member, and once fields are
+ * read their staging of at most 64 MiB); max_members in [1, 65536]; hip_stream as for
+ * lbib_create. */
 lbib_status lbib_pool_create(int32_t precision, int64_t hbm_budget_bytes, int32_t max_members, void* hip_stream,
                              lbib_pool_handle* out);
 

@@ -200,22 +200,14 @@ __device__ __forceinline__ void neq_encode(T* fout, const SweepArgs& a, int i, i
     }
 }
 
-// Push layout: collide node (i, j), whose populations update_load presented, and scatter
-// its results to the neighbours, with half-way bounce-back at the two walls and periodic x.
-// COH: coherent stores (a concurrently running launch reads the results).
-template <typename T, bool COH = false>
-__device__ __forceinline__ void push_update(T* __restrict__ fout, const SweepArgs& a, int i, int j,
-                                            const typename St<T>::C (&g)[9], double Fx, double Fy)
+// Push layout: scatter the post-collision values of node (i, j) (c: its columns; j
+// wave-uniform) to the neighbours, with half-way bounce-back at the two walls and periodic x.
+template <typename T>
+__device__ __forceinline__ void push_store(T* __restrict__ fout, const SweepArgs& a, const Cols& c, int j,
+                                           const typename St<T>::C (&post)[9], int pol)
 {
     using C = typename St<T>::C;
-    j = wave_row(j);
     const int64_t P = a.plane, R = a.pitch;
-    const int pol = COH ? ST_COH : ST_PLAIN;
-    C post[9], m[3];
-    collide_node<C>(g, a, (C)Fx, (C)Fy, post, m);
-    neq_encode<T, C>(fout, a, i, j, m, post, pol);
-
-    const Cols c = cols<T>(i, a.nx);
     const bool top = (j + 1 == a.ny), bot = (j == 0);
     const double sc = a.scale;
     auto out = [&](T* b, uint32_t o, C v) { st_store(at(b, o), 0, v, sc, pol); };
@@ -237,6 +229,35 @@ __device__ __forceinline__ void push_update(T* __restrict__ fout, const SweepArg
     out(bot ? b[6] : snext(b[8], -R), opaque(bot ? c.o[1] : c.o[2]), post[8]);
 }
 
+// Push layout: collide node (i, j), whose populations update_load presented, and scatter its
+// results.  COH: coherent stores (a concurrently running launch reads the results).
+template <typename T, bool COH = false>
+__device__ __forceinline__ void push_update(T* __restrict__ fout, const SweepArgs& a, int i, int j,
+                                            const typename St<T>::C (&g)[9], double Fx, double Fy)
+{
+    using C = typename St<T>::C;
+    j = wave_row(j);
+    const int pol = COH ? ST_COH : ST_PLAIN;
+    C post[9], m[3];
+    collide_node<C>(g, a, (C)Fx, (C)Fy, post, m);
+    neq_encode<T, C>(fout, a, i, j, m, post, pol);
+    push_store<T>(fout, a, cols<T>(i, a.nx), j, post, pol);
+}
+
+// Pull layout: store the post-collision values at the node itself (o: the byte offset of its
+// column; j wave-uniform).
+template <typename T>
+__device__ __forceinline__ void pull_store(T* __restrict__ fout, const SweepArgs& a, uint32_t o, int j,
+                                           const typename St<T>::C (&post)[9], int pol)
+{
+    T* b = sbase(fout + (int64_t)j * a.pitch);
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        st_store(at(b, o), 0, post[q], a.scale, pol);
+        if (q < 8) b = snext(b, a.plane);
+    }
+}
+
 // Pull layout: collide node (i, j), whose inflow update_load gathered from the previous
 // step's post-collision values (bounce-back across the walls), and store the post-collision
 // values at (i, j) itself.  Every store is aligned and each value is written once, so both
@@ -251,13 +272,7 @@ __device__ __forceinline__ void pull_update(T* __restrict__ fout, const SweepArg
     C post[9], m[3];
     collide_node<C>(g, a, (C)Fx, (C)Fy, post, m);
     neq_encode<T, C>(fout, a, i, j, m, post, pol);
-    T* b = sbase(fout + (int64_t)j * a.pitch);
-    const uint32_t o = (uint32_t)i * (uint32_t)sizeof(T);
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        st_store(at(b, o), 0, post[q], a.scale, pol);
-        if (q < 8) b = snext(b, a.plane);
-    }
+    pull_store<T>(fout, a, (uint32_t)i * (uint32_t)sizeof(T), j, post, pol);
 }
 
 // The populations of node (i, j) at the start of a step in the compute type, read past the

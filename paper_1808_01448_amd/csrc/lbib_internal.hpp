@@ -25,7 +25,7 @@ struct DevParticle {
     double xc, yc, th, ux, uy, om;        // level n
     double xc1, yc1, th1, ux1, uy1, om1;  // level n-1
     int64_t step;                         // n: the next step to run
-    int32_t pad0, pad1;
+    int32_t buf, pad1;                    // a pool member: the buffer that holds level n (0 fA, 1 fB)
     lbib_particle_state last;             // record of the last completed step
 };
 
@@ -336,21 +336,29 @@ hipError_t launch_particle_fused(const ParticleArgs<T>* args, int32_t n, int32_t
                                  unsigned long long* pmask, int32_t max_nl, size_t lds, unsigned long long* bar,
                                  unsigned long long target, hipStream_t stream);
 
-// A pool of independent simulations stepped together (one launch per kernel per step).
+// A pool of independent simulations stepped together, one step or two at a time.
 // The particle launch runs member active[b] in workgroup b and copies the member's box
-// descriptor of the step into ctl[member], with `pad` set to the parity of the step it ran
-// (its input buffer: 0 fA, 1 fB), or only pad = -1 when the member did not step (target
-// reached, or frozen by its watchdog).  The sweep's blocks are listed in `table`: (member,
-// first tile); a block sweeps up to TPB consecutive tiles of BX x 256/BX nodes of that
-// member, reading ctl[member] and the member's record side by side.
+// descriptor of the step into ctl[member], with `pad` set to the buffer that held the step's
+// populations (0 fA, 1 fB), or only pad = -1 when the member did not step (target reached, or
+// frozen by its watchdog).  The one-step sweep's blocks are listed in `table`: (member, first
+// tile); a block sweeps up to TPB consecutive tiles of BX x 256/BX nodes of that member,
+// reading ctl[member] and the member's record side by side.
+// Two steps (n, n+1): the first particle launch; a zone launch that sweeps step n around the
+// box of step n+1 only, into the other buffer; the second particle launch, which reads the
+// other buffer there and leaves its box in the second half of ctl and its force in tile_b; and
+// a sweep of both steps in one pass (march_pair), which reads the first buffer and overwrites
+// the other.  A member with one step left (or whose watchdog fired in the first) steps once.
 template <typename T>
 struct PoolSweep {
     SweepArgs a;
-    T* fA;  // buffer of the even steps
-    T* fB;  // buffer of the odd steps
+    T* fA;
+    T* fB;
     const int64_t* tile;
+    int64_t* tile_b;        // the second step's force tile
+    const TileDesc* zone;   // the second step's box, as the first predicted it
     FastDiv gx;      // tiles along x
     int32_t ntiles;  // tiles of this member
+    FastDiv px;      // blocks of the two-step sweep along x
 };
 // Sweep configurations a pool can use: tile width BX in {64, 128, 256} nodes (256/BX rows),
 // TPB in {1, 2, 4, 8} tiles per block.
@@ -358,13 +366,25 @@ struct PoolSweepConfig {
     int32_t bx, tpb;
 };
 // lds: the dynamic LDS of the launch (the most particle_launch_lds of the members).
+constexpr int kPairStrip = 62;  // result columns of a wave of the two-step sweeps (lbib_march.hpp)
+// half: 0 the step (or the first of two), 1 the second of two.
 template <typename T>
-hipError_t launch_pool_particle(const ParticleArgs<T>* args, const int32_t* active, TileDesc* ctl, int32_t n_active,
-                                int32_t max_nl, size_t lds, hipStream_t stream, hipEvent_t t0 = nullptr,
-                                hipEvent_t t1 = nullptr);
+hipError_t launch_pool_particle(const ParticleArgs<T>* args, const PoolSweep<T>* sims, const int32_t* active,
+                                TileDesc* ctl, int32_t n_active, int32_t half, int32_t max_nl, size_t lds,
+                                hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 template <typename T>
 hipError_t launch_pool_sweep(const PoolSweep<T>* sims, const TileDesc* ctl, const int2* table, int32_t n_blocks,
                              PoolSweepConfig cfg, hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// The two-step sweep: a workgroup of four waves takes four strips of kPairStrip columns by a run
+// of pool_pair_rows(cfg) rows; table: (member, block).  Not for the f - f_eq storages
+// (hipErrorInvalidValue).
+int32_t pool_pair_rows(PoolSweepConfig cfg);
+template <typename T>
+hipError_t launch_pool_zone(const PoolSweep<T>* sims, const TileDesc* ctl, int32_t n_active, hipStream_t stream);
+template <typename T>
+hipError_t launch_pool_pair(const PoolSweep<T>* sims, const TileDesc* ctl, int32_t n_active, const int2* table,
+                            int32_t n_blocks, PoolSweepConfig cfg, hipStream_t stream, hipEvent_t t0 = nullptr,
+                            hipEvent_t t1 = nullptr);
 
 hipError_t launch_philox(const uint32_t* ctr, const uint32_t* key, uint32_t* out, int64_t n, hipStream_t stream);
 hipError_t launch_mls(const double* pts, int64_t n, int32_t nx, int32_t ny, int32_t* node, double* phi, double* psix,

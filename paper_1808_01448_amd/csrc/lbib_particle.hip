@@ -1493,54 +1493,68 @@ hipError_t launch_particle_fused(const ParticleArgs<T>* args, int32_t n, int32_t
 // k = active[b].  A member whose step counter has reached its target, or whose watchdog
 // has raised a flag, does nothing (ctl[k].pad = -1: its sweep does nothing either), so a
 // failed member stays frozen at the step that failed.  Otherwise ctl[k] receives the box
-// descriptor of step n with pad = the parity of n: the populations of step n are in f for
-// even n and in fB for odd n.
+// descriptor of step n with pad = the buffer that holds the populations of step n (0 f, 1 fB),
+// and the state records that the other buffer will hold the level its sweep reaches.  half 1
+// (the second of two steps swept together, PoolSweep): reads that other buffer, whose zone the
+// zone launch has filled, checks its box against the one the first half predicted, and leaves
+// the box in the second half of ctl and the force in tile_b.
 template <typename T, int MPT>
 __global__ __launch_bounds__(PB) void pool_particle_kernel(const ParticleArgs<T>* __restrict__ args,
+                                                           const PoolSweep<T>* __restrict__ sims,
                                                            const int32_t* __restrict__ active,
-                                                           TileDesc* __restrict__ ctl, uint32_t lds_bytes)
+                                                           TileDesc* __restrict__ ctl, int half, uint32_t lds_bytes)
 {
     extern __shared__ double lds_dyn[];
     const int k = active[blockIdx.x];
+    TileDesc* const c = ctl + (half ? (int)gridDim.x + k : k);
     ParticleArgs<T> a = args[k];
     const int64_t n = a.st->step;
     if (n >= a.target_steps || *a.flags != 0) {
-        if (threadIdx.x == 0) ctl[k].pad = -1;
+        if (threadIdx.x == 0) c->pad = -1;
         return;
     }
-    a.f = (n & 1) ? a.fB : a.f;
+    const int buf = a.st->buf;
+    a.f = buf ? a.fB : a.f;
+    if (half) {
+        a.tile = sims[k].tile_b;
+        a.parity_in = 1;
+        a.parity_out = 0;
+        a.check_zone = 1;
+    }
     particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes);
     if (threadIdx.x == 0) {  // the thread that wrote *a.desc in the particle phase
         TileDesc d = coherent_load(a.desc);
-        d.pad = (int32_t)(n & 1);
-        ctl[k] = d;
+        d.pad = buf;
+        *c = d;
+        if (!half) a.st->buf = buf ^ 1;
     }
 }
 
 template <typename T, int MPT>
-hipError_t launch_pool_mpt(const ParticleArgs<T>* args, const int32_t* active, TileDesc* ctl, int32_t n_active,
-                           size_t lds, hipStream_t stream, hipEvent_t t0, hipEvent_t t1)
+hipError_t launch_pool_mpt(const ParticleArgs<T>* args, const PoolSweep<T>* sims, const int32_t* active, TileDesc* ctl,
+                           int32_t n_active, int32_t half, size_t lds, hipStream_t stream, hipEvent_t t0, hipEvent_t t1)
 {
     static bool attr = false;
     hipError_t e = allow_max_lds(pool_particle_kernel<T, MPT>, attr);
     if (e != hipSuccess) return e;
     if (t0 || t1)
         hipExtLaunchKernelGGL((pool_particle_kernel<T, MPT>), dim3(n_active), dim3(PB), (uint32_t)lds, stream, t0, t1,
-                              0u, args, active, ctl, (uint32_t)lds);
+                              0u, args, sims, active, ctl, (int)half, (uint32_t)lds);
     else
-        hipLaunchKernelGGL((pool_particle_kernel<T, MPT>), dim3(n_active), dim3(PB), lds, stream, args, active, ctl,
-                           (uint32_t)lds);
+        hipLaunchKernelGGL((pool_particle_kernel<T, MPT>), dim3(n_active), dim3(PB), lds, stream, args, sims, active,
+                           ctl, (int)half, (uint32_t)lds);
     return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_pool_particle(const ParticleArgs<T>* args, const int32_t* active, TileDesc* ctl, int32_t n_active,
-                                int32_t max_nl, size_t lds, hipStream_t stream, hipEvent_t t0, hipEvent_t t1)
+hipError_t launch_pool_particle(const ParticleArgs<T>* args, const PoolSweep<T>* sims, const int32_t* active,
+                                TileDesc* ctl, int32_t n_active, int32_t half, int32_t max_nl, size_t lds,
+                                hipStream_t stream, hipEvent_t t0, hipEvent_t t1)
 {
     if (n_active <= 0) return hipSuccess;
     if (lds > kLdsMax || lds < kLdsHead) return hipErrorInvalidValue;
-    if (max_nl <= PB) return launch_pool_mpt<T, 1>(args, active, ctl, n_active, lds, stream, t0, t1);
-    if (max_nl <= 2 * PB) return launch_pool_mpt<T, 2>(args, active, ctl, n_active, lds, stream, t0, t1);
+    if (max_nl <= PB) return launch_pool_mpt<T, 1>(args, sims, active, ctl, n_active, half, lds, stream, t0, t1);
+    if (max_nl <= 2 * PB) return launch_pool_mpt<T, 2>(args, sims, active, ctl, n_active, half, lds, stream, t0, t1);
     return hipErrorInvalidValue;
 }
 
@@ -1714,8 +1728,9 @@ hipError_t launch_copy(const float4* src, float4* dst, int64_t n, hipStream_t st
 }
 
 #define LBIB_PARTICLE_INSTANTIATE(T)                                                                        \
-    template hipError_t launch_pool_particle<T>(const ParticleArgs<T>*, const int32_t*, TileDesc*, int32_t,      \
-                                                int32_t, size_t, hipStream_t, hipEvent_t, hipEvent_t);          \
+    template hipError_t launch_pool_particle<T>(const ParticleArgs<T>*, const PoolSweep<T>*, const int32_t*,     \
+                                                TileDesc*, int32_t, int32_t, int32_t, size_t, hipStream_t,       \
+                                                hipEvent_t, hipEvent_t);                                         \
     template hipError_t launch_particle<T>(const ParticleArgs<T>&, hipStream_t, hipEvent_t, hipEvent_t);        \
     template hipError_t launch_particle_run<T>(const ParticleArgs<T>&, const ParticleRun<T>&, hipStream_t,      \
                                                hipEvent_t, hipEvent_t);                                          \

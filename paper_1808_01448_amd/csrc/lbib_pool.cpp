@@ -1,6 +1,7 @@
 // lbib_pool.cpp -- many independent LB-IB adhesion simulations stepped together: one
 // particle-phase launch (one workgroup per member) and one lattice-sweep launch (the tiles
-// of every member) per time step, instead of two launches and two launch gaps per member.
+// of every member) per time step, instead of two launches and two launch gaps per member;
+// large pools sweep two steps in one pass over memory (PoolSweep).
 // Members differ in lattice size, particle, ligands and seed, join and leave between
 // calls, and each runs its own number of steps; every member's result is bit-identical to
 // the same simulation run alone through lbib_create / lbib_step (serial schedule), since
@@ -137,6 +138,13 @@ struct lbib_pool {
     size_t sims_cap = 0;
     int2* d_table = nullptr;
     size_t table_cap = 0;
+    // two steps per sweep (PoolSweep): its block table and the members' second force tiles
+    bool pairs = false;
+    int2* d_ptable = nullptr;
+    size_t ptable_cap = 0;
+    int32_t n_pblocks = 0;
+    int64_t* d_tile_b = nullptr;
+    size_t tile_b_cap = 0;
     TileDesc* d_ctl = nullptr;  // per running member: its box of the step and the step parity
     size_t ctl_cap = 0;
     int32_t n_active = 0, n_blocks = 0, max_nl = 0;
@@ -199,6 +207,26 @@ void ensure(T*& d, size_t& cap, size_t need, hipError_t& e)
     if (e == hipSuccess) cap = c;
 }
 
+// Whether the pool's sweeps take two steps in one pass over memory: from kPairBytes of traffic
+// per step.  The pass saves most of every second step's traffic, and costs the zone launch, a
+// wave's march over its rows in turn and two extra rows per run, which smaller pools do not get
+// back (us per step, one step per sweep against two, with the particle launches: 59 MB FP32 37.0
+// against 39.8, 75 MB 37.5 / 39.2, 118 MB 49.3 / 41.9, 302 MB 84 / 65, 944 MB 210 / 138; FP64
+// 118 MB 48.8 / 45.3, FP16 75 MB 39.2 / 42.9, 118 MB 47.5 / 44.6).  The f - f_eq storages keep
+// one step (their sweep is not bound by traffic), as do rows whose window exceeds a buffer
+// resource's bound.
+constexpr double kPairBytes = 100e6;
+template <typename T>
+bool pair_sweeps(const std::vector<Member*>& run)
+{
+    double bytes = 0.0;
+    for (const Member* m : run) {
+        if (3 * (int64_t)m->g.pitch * (int64_t)sizeof(typename St<T>::raw) >= (int64_t)1 << 31) return false;
+        bytes += (double)m->g.upd_bytes * m->g.nx * m->g.ny;
+    }
+    return !St<T>::neq && bytes >= kPairBytes;
+}
+
 // Rebuild the launch tables from the running members (the stream is idle when called).
 // Members with the most markers come first so the longest particle phases start first.
 template <typename T>
@@ -211,7 +239,10 @@ lbib_status rebuild(lbib_pool* h)
     std::vector<ParticleArgs<T>> args(run.size());
     std::vector<int32_t> active(run.size());
     std::vector<PoolSweep<T>> sims(run.size());
-    std::vector<int2> table;
+    std::vector<int2> table, ptable;
+    std::vector<size_t> tile_off(run.size());
+    size_t tile_elems = 0;
+    const int prows = pool_pair_rows(h->cfg);
     int32_t max_nl = 0;
     size_t lds_bytes = 0;
     for (size_t k = 0; k < run.size(); ++k) {
@@ -240,8 +271,26 @@ lbib_status rebuild(lbib_pool* h)
         if ((int64_t)table.size() + s.ntiles / h->cfg.tpb + 1 > 0x7fffffff)
             return fail(h, LBIB_E_INVALID, "pool: more than 2^31 sweep blocks");
         for (int32_t t = 0; t < s.ntiles; t += h->cfg.tpb) table.push_back(make_int2((int)k, t));
+        s.zone = m.p.d_zone;
+        tile_off[k] = tile_elems;
+        tile_elems += 2 * (size_t)m.p.box_cap;
+        const int px = (m.g.nx + 4 * kPairStrip - 1) / (4 * kPairStrip);
+        const int py = (m.g.ny + prows - 1) / prows;
+        s.px = make_fastdiv((uint32_t)px);
+        for (int32_t t = 0; t < px * py; ++t) ptable.push_back(make_int2((int)k, t));
     }
     hipError_t e = hipSuccess;
+    h->pairs = pair_sweeps<T>(run);
+    if (h->pairs) {
+        ensure(h->d_ptable, h->ptable_cap, ptable.size(), e);
+        ensure(h->d_tile_b, h->tile_b_cap, tile_elems, e);
+        if (e == hipErrorOutOfMemory) {  // no room for the second tiles: one step at a time
+            (void)hipGetLastError();
+            e = hipSuccess;
+            h->pairs = false;
+        }
+        for (size_t k = 0; h->pairs && k < run.size(); ++k) sims[k].tile_b = h->d_tile_b + tile_off[k];
+    }
     ParticleArgs<T>* dargs = (ParticleArgs<T>*)h->d_args;
     PoolSweep<T>* dsims = (PoolSweep<T>*)h->d_sims;
     ensure(dargs, h->args_cap, args.size(), e);
@@ -250,16 +299,19 @@ lbib_status rebuild(lbib_pool* h)
     ensure(dsims, h->sims_cap, sims.size(), e);
     h->d_sims = dsims;
     ensure(h->d_table, h->table_cap, table.size(), e);
-    ensure(h->d_ctl, h->ctl_cap, run.size(), e);
+    ensure(h->d_ctl, h->ctl_cap, 2 * run.size(), e);
     if (e != hipSuccess) return hip_fail(h, e, "pool: table allocation");
     if (!run.empty()) {
         PCHK(h, hipMemcpy(h->d_args, args.data(), args.size() * sizeof(ParticleArgs<T>), hipMemcpyHostToDevice));
         PCHK(h, hipMemcpy(h->d_active, active.data(), active.size() * sizeof(int32_t), hipMemcpyHostToDevice));
         PCHK(h, hipMemcpy(h->d_sims, sims.data(), sims.size() * sizeof(PoolSweep<T>), hipMemcpyHostToDevice));
         PCHK(h, hipMemcpy(h->d_table, table.data(), table.size() * sizeof(int2), hipMemcpyHostToDevice));
+        if (h->pairs)
+            PCHK(h, hipMemcpy(h->d_ptable, ptable.data(), ptable.size() * sizeof(int2), hipMemcpyHostToDevice));
     }
     h->n_active = (int32_t)run.size();
     h->n_blocks = (int32_t)table.size();
+    h->n_pblocks = (int32_t)ptable.size();
     h->max_nl = max_nl;
     h->lds_bytes = lds_bytes;
     h->dirty = false;
@@ -272,25 +324,48 @@ struct EvPair {
     hipEvent_t t0 = nullptr, t1 = nullptr;
 };
 
-EvPair next_events(lbib_pool* h, int kind)
+// steps: the steps the launch covers, counted as that many launches.
+EvPair next_events(lbib_pool* h, int kind, int64_t steps = 1)
 {
     EvPair p;
     if (!h->timing || h->ev_used[kind] + 2 > h->ev[kind].size()) return p;
     p.t0 = h->ev[kind][h->ev_used[kind]];
     p.t1 = h->ev[kind][h->ev_used[kind] + 1];
     h->ev_used[kind] += 2;
-    h->launches[kind] += 1;
+    h->launches[kind] += steps;
     return p;
 }
 
 template <typename T>
-hipError_t launch_step(lbib_pool* h, EvPair e1, EvPair e0)
+hipError_t launch_half(lbib_pool* h, int32_t half)
 {
-    hipError_t e = launch_pool_particle<T>((const ParticleArgs<T>*)h->d_args, h->d_active, h->d_ctl, h->n_active,
-                                           h->max_nl, h->lds_bytes, h->stream, e1.t0, e1.t1);
-    if (e != hipSuccess) return e;
-    return launch_pool_sweep<T>((const PoolSweep<T>*)h->d_sims, h->d_ctl, h->d_table, h->n_blocks, h->cfg, h->stream,
-                                e0.t0, e0.t1);
+    const EvPair ev = next_events(h, 1);
+    return launch_pool_particle<T>((const ParticleArgs<T>*)h->d_args, (const PoolSweep<T>*)h->d_sims, h->d_active,
+                                   h->d_ctl, h->n_active, half, h->max_nl, h->lds_bytes, h->stream, ev.t0, ev.t1);
+}
+
+// The launches of n pool steps: two at a time where the pool sweeps pairs, a last odd one alone.
+template <typename T>
+hipError_t launch_steps(lbib_pool* h, int64_t n)
+{
+    const PoolSweep<T>* sims = (const PoolSweep<T>*)h->d_sims;
+    hipError_t e = hipSuccess;
+    while (n > 0 && e == hipSuccess) {
+        if ((e = launch_half<T>(h, 0)) != hipSuccess) break;
+        if (h->pairs && n >= 2) {
+            if ((e = launch_pool_zone<T>(sims, h->d_ctl, h->n_active, h->stream)) != hipSuccess) break;
+            if ((e = launch_half<T>(h, 1)) != hipSuccess) break;
+            const EvPair e0 = next_events(h, 0, 2);
+            e = launch_pool_pair<T>(sims, h->d_ctl, h->n_active, h->d_ptable, h->n_pblocks, h->cfg, h->stream, e0.t0,
+                                    e0.t1);
+            n -= 2;
+        } else {
+            const EvPair e0 = next_events(h, 0);
+            e = launch_pool_sweep<T>(sims, h->d_ctl, h->d_table, h->n_blocks, h->cfg, h->stream, e0.t0, e0.t1);
+            n -= 1;
+        }
+    }
+    return e;
 }
 
 // Capture graph_steps steps of direct launches into one executable graph.
@@ -299,8 +374,7 @@ lbib_status build_graph(lbib_pool* h)
 {
     hipGraph_t g = nullptr;
     PCHK(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
-    hipError_t e = hipSuccess;
-    for (int32_t k = 0; k < h->graph_steps && e == hipSuccess; ++k) e = launch_step<T>(h, EvPair{}, EvPair{});
+    hipError_t e = launch_steps<T>(h, h->graph_steps);  // a pool with timing on captures no graph
     hipError_t e2 = hipStreamEndCapture(h->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -333,11 +407,7 @@ lbib_status enqueue(lbib_pool* h, int64_t n)
         }
         for (; k + h->graph_steps <= n; k += h->graph_steps) PCHK(h, hipGraphLaunch(h->graph, h->stream));
     }
-    for (; k < n; ++k) {
-        const EvPair e1 = next_events(h, 1);
-        const EvPair e0 = next_events(h, 0);
-        PCHK(h, launch_step<T>(h, e1, e0));
-    }
+    PCHK(h, launch_steps<T>(h, n - k));
     h->pool_steps += n;
     return LBIB_OK;
 }
@@ -613,7 +683,7 @@ lbib_status lbib_pool_read_field(lbib_pool_handle h, int32_t slot, int32_t which
         PCHK(h, hipStreamSynchronize(h->stream));
         DevParticle st;
         PCHK(h, hipMemcpy(&st, m->p.d_st, sizeof(st), hipMemcpyDeviceToHost));
-        PCHK(h, read_field((st.step & 1) ? m->fB : m->fA, m->g, which, out, h->stage, h->stream));
+        PCHK(h, read_field(st.buf ? m->fB : m->fA, m->g, which, out, h->stage, h->stream));
     } catch (const std::bad_alloc&) {
         return fail(h, LBIB_E_NOMEM, "lbib_pool_read_field: host allocation failed");
     }
@@ -833,6 +903,8 @@ void lbib_pool_destroy(lbib_pool_handle h)
     if (h->d_sims) (void)hipFree(h->d_sims);
     dfree(h->d_active);
     dfree(h->d_table);
+    dfree(h->d_ptable);
+    dfree(h->d_tile_b);
     dfree(h->d_ctl);
     dfree(h->stage.p);
     if (h->graph) (void)hipGraphExecDestroy(h->graph);
