@@ -553,4 +553,27 @@ __device__ __forceinline__ bool in_box(const TileDesc& d, int i, int j, int nx)
     return di < d.w && dj >= 0 && dj < d.h;
 }
 
+// Adds the spread force at node (i, j) of the particle of box d, from its compact list and the
+// list's index (PartRef).  COHERENT: written by a workgroup running beside this one.
+template <bool COHERENT>
+__device__ __forceinline__ void box_force(const TileDesc& d, const int64_t* __restrict__ tile,
+                                          const uint2* __restrict__ ring, int i, int j, int nx, double& Fx, double& Fy)
+{
+    if (!(d.active && in_box(d, i, j, nx))) return;
+    int di = i - d.i0w;
+    if (di < 0) di += nx;
+    const int n = (j - d.j0) * d.w + di;
+    uint2 r;
+    if (COHERENT) {
+        const uint64_t e = (uint64_t)coherent_load((const int64_t*)(ring + (n >> 5)));
+        r = make_uint2((uint32_t)e, (uint32_t)(e >> 32));
+    } else {
+        r = ring[n >> 5];
+    }
+    if (!((r.x >> (n & 31)) & 1u)) return;  // no support of the particle reaches the node
+    const int64_t* t = tile + 2 * ((int)r.y + __popc(r.x & ((1u << (n & 31)) - 1u)));
+    Fx += ldexp((double)(COHERENT ? coherent_load(t) : t[0]), -d.scale);
+    Fy += ldexp((double)(COHERENT ? coherent_load(t + 1) : t[1]), -d.scale);
+}
+
 }  // namespace lbib

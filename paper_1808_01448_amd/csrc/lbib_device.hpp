@@ -367,8 +367,22 @@ template <typename T, typename R>
 __device__ __forceinline__ void load_node(const T* f, int i, int j, int nx, int ny, int pitch, int64_t plane, bool pull,
                                           double inv_scale, double uw6, bool nt, R (&g)[9])
 {
+    // pop_index, from one address per node
+    const T* p = f + ((int64_t)j * pitch + i);
+    if (!pull) {
 #pragma unroll
-    for (int q = 0; q < 9; ++q) g[q] = (R)st_load(f, pop_index(q, i, j, nx, ny, pitch, plane, pull), inv_scale, nt);
+        for (int q = 0; q < 9; ++q) g[q] = (R)st_load(p + q * plane, 0, inv_scale, nt);
+    } else {
+        const int left = i == 0 ? nx - 1 : -1, right = i == nx - 1 ? 1 - nx : 1;  // to columns i - 1, i + 1
+        const bool bot = j == 0, top = j == ny - 1;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const bool wall = kEy[q] > 0 ? bot : kEy[q] < 0 ? top : false;
+            const int dx = kEx[q] > 0 ? left : kEx[q] < 0 ? right : 0;
+            const int64_t off = wall ? kOpp[q] * plane : q * plane - (int64_t)kEy[q] * pitch + dx;
+            g[q] = (R)st_load(p + off, 0, inv_scale, nt);
+        }
+    }
     if constexpr (St<T>::neq) {
         const float* m = neq_moments(f, pitch, plane, ny);
         const int64_t mp = neq_mpitch(pitch, plane);

@@ -32,7 +32,7 @@ struct DevParticle {
 // The particle's box: every node that an MLS support of a marker or probe of one step
 // reaches, nodes i0w + di (mod nx), j0 + dj for 0 <= di < w, 0 <= dj < h (i0u is the same
 // origin before wrapping).  The spread force on the box is 64-bit fixed point, value =
-// q * 2^-scale, laid out [dj][di][2].
+// q * 2^-scale.
 struct TileDesc {
     int32_t i0w, j0, w, h;
     int32_t scale;
@@ -153,7 +153,7 @@ struct SweepArgs {
     float omega_f, keep_f, b3_f, b9_f, inv_scale_f;
 };
 
-// Where the sweep and the probes of a multi-particle step find particle p's spread force:
+// Where the sweep, and the probes of a multi-particle step, find particle p's spread force:
 // the box node n = dj w + di carries a force when bit n % 32 of ring[n / 32].x is set; it is
 // then entry s = ring[n / 32].y + (set bits below n % 32) of the compact list tile[2 s],
 // tile[2 s + 1] (64-bit fixed point, value q 2^-scale).
@@ -186,9 +186,9 @@ struct ParticleArgs {
     double sigma, sigma_star, y_cr, y_eq, k_f, k_r0, kBT, hamaker;
     uint64_t seed;
     uint32_t pid;
-    int64_t* tile;      // [box_cap][2] fixed-point spread force on the box (read by the sweep); in
-                        // the split phase, the compact list of the nodes the marker supports reach
-    uint2* ring;        // split phase: the index of that list (PartRef)
+    int64_t* tile;      // [box_cap][2] fixed-point spread force: the compact list of the box nodes
+                        // that the launch's supports reach (read by the sweep)
+    uint2* ring;        // the index of that list (PartRef)
     double* box_global;  // node fields and node map of up to box_cap nodes when they may not fit in LDS
     int32_t box_cap;     // node capacity of the box
     TileDesc* desc;      // this step's box
@@ -254,6 +254,7 @@ struct HandoverArgs {
     uint32_t zone_tag;
     const TileDesc* desc;
     const int64_t* tile;
+    const uint2* ring;
     const unsigned long long* ready;
     unsigned long long ready_target;
     unsigned long long* zdone;
@@ -270,13 +271,14 @@ template <typename T>
 hipError_t launch_sweep_multi(const T* fin, T* fout, const SweepArgs& a, const unsigned long long* mcur,
                               unsigned long long* mnext, const PartRef* refs, bool pull, hipStream_t stream,
                               hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
-// Sweep of every node, with the spread force of desc / tile when desc != NULL.  t0 / t1
+// Sweep of every node, with the spread force of desc / tile / ring (PartRef) when desc != NULL.  t0 / t1
 // (optional) receive the kernel's own start and end times.  pull selects the layout of the
 // population buffers (pop_index in lbib_device.hpp); rev, the reverse tile order
 // (reverse_sweep).
 template <typename T>
-hipError_t launch_sweep(const T* fin, T* fout, const SweepArgs& a, const TileDesc* desc, const int64_t* tile, bool pull,
-                        hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr, bool rev = false);
+hipError_t launch_sweep(const T* fin, T* fout, const SweepArgs& a, const TileDesc* desc, const int64_t* tile,
+                        const uint2* ring, bool pull, hipStream_t stream, hipEvent_t t0 = nullptr,
+                        hipEvent_t t1 = nullptr, bool rev = false);
 // LDS of the particle phase.  particle_lds_aux_bytes: the node mask, its prefix counts, the
 // fill queues and the overlap list, which must not exceed 158 KB.  particle_lds_bytes: that
 // plus the node fields of every node of a box of box_cap nodes, or 0 when this exceeds
@@ -345,16 +347,19 @@ hipError_t launch_particle_fused(const ParticleArgs<T>* args, int32_t n, int32_t
 // reading ctl[member] and the member's record side by side.
 // Two steps (n, n+1): the first particle launch; a zone launch that sweeps step n around the
 // box of step n+1 only, into the other buffer; the second particle launch, which reads the
-// other buffer there and leaves its box in the second half of ctl and its force in tile_b; and
-// a sweep of both steps in one pass (march_pair), which reads the first buffer and overwrites
-// the other.  A member with one step left (or whose watchdog fired in the first) steps once.
+// other buffer there and leaves its box in the second half of ctl and its force in tile_b and
+// ring_b; and a sweep of both steps in one pass (march_pair), which reads the first buffer and
+// overwrites the other.  A member with one step left (or whose watchdog fired in the first)
+// steps once.
 template <typename T>
 struct PoolSweep {
     SweepArgs a;
     T* fA;
     T* fB;
     const int64_t* tile;
-    int64_t* tile_b;        // the second step's force tile
+    const uint2* ring;
+    int64_t* tile_b;        // the second step's force list and its index
+    uint2* ring_b;
     const TileDesc* zone;   // the second step's box, as the first predicted it
     FastDiv gx;      // tiles along x
     int32_t ntiles;  // tiles of this member

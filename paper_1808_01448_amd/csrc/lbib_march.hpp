@@ -89,11 +89,12 @@ __device__ __forceinline__ V from_right(V v)
     return lane_shift_v<0x130>(v);  // DPP wave_shl:1
 }
 
-// The spread force of one of the two steps: the particle's box and its dense tile (d.active 0:
-// none).
+// The spread force of one of the two steps: the particle's box and its force (PartRef; d.active
+// 0: none).
 struct BoxForce {
     TileDesc d;
     const int64_t* tile;
+    const uint2* ring;
 };
 
 // The rows of a buffer around row j, as a buffer resource: a segment (row j - 1 + dr, population
@@ -209,15 +210,7 @@ __device__ __forceinline__ void march_pair(const T* __restrict__ fin, T* __restr
     const bool any1 = col_in(f1.d), any2 = col_in(f2.d);
     auto force = [&](const BoxForce& f, bool any, int j, C& Fx, C& Fy) {
         double x = a.gx, y = a.gy;
-        if (any && j >= f.d.j0 && j < f.d.j0 + f.d.h) {
-            int di = i - f.d.i0w;
-            if (di < 0) di += a.nx;
-            if (di < f.d.w) {
-                const int64_t* t = f.tile + 2 * ((size_t)(j - f.d.j0) * f.d.w + di);
-                x += ldexp((double)t[0], -f.d.scale);
-                y += ldexp((double)t[1], -f.d.scale);
-            }
-        }
+        if (any && j >= f.d.j0 && j < f.d.j0 + f.d.h) box_force<false>(f.d, f.tile, f.ring, i, j, a.nx, x, y);
         Fx = (C)x;
         Fy = (C)y;
     };

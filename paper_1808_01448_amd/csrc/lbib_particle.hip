@@ -31,61 +31,67 @@ using namespace dev;
 constexpr int PB = 512;       // threads of the particle workgroup
 constexpr int NW = PB / 64;   // wavefronts per workgroup
 
+// The value of lane l ^ O for a value that lanes l and l ^ 2 O already share (O = 8 and below; at
+// O = 32 and 16 any value), by register permutes: the butterfly's steps are O = 32, 16, ..., 1.
+// (Through LDS, as __shfl_xor goes, a step costs an LDS round trip: the six sums of the loads
+// took 1.9 us of the phase that way.)
+template <int O>
+__device__ __forceinline__ uint32_t partner(uint32_t v)
+{
+    if constexpr (O == 32) {
+        const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return (threadIdx.x & 32) ? p[0] : p[1];
+    } else if constexpr (O == 16) {
+        const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (threadIdx.x & 16) ? p[0] : p[1];
+    } else {
+        // DPP row_ror:8, row_ror:4, quad_perm [2,3,0,1], quad_perm [1,0,3,2]
+        constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4E : 0xB1;
+        return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, ctrl, 0xf, 0xf, false);
+    }
+}
+template <int O>
+__device__ __forceinline__ int partner(int v)
+{
+    return (int)partner<O>((uint32_t)v);
+}
+template <int O>
+__device__ __forceinline__ double partner(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = partner<O>((uint32_t)u), hi = partner<O>((uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+template <typename V, typename F>
+__device__ __forceinline__ V wave_reduce(V v, F f)
+{
+    v = f(v, partner<32>(v));
+    v = f(v, partner<16>(v));
+    v = f(v, partner<8>(v));
+    v = f(v, partner<4>(v));
+    v = f(v, partner<2>(v));
+    return f(v, partner<1>(v));
+}
+
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](double a, double b) { return a + b; });
 }
-
 __device__ __forceinline__ int wave_isum(int v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](int a, int b) { return a + b; });
 }
-
 __device__ __forceinline__ int wave_ior(int v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v |= __shfl_xor(v, o, 64);
-    return v;
+    return wave_reduce(v, [](int a, int b) { return a | b; });
 }
-
 __device__ __forceinline__ int wave_imin(int v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
+    return wave_reduce(v, [](int a, int b) { return min(a, b); });
 }
-
 __device__ __forceinline__ double wave_max(double v)
 {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
-// Sum of N doubles over the workgroup; every thread receives the totals.
-template <int N>
-__device__ __forceinline__ void block_sum(double (&v)[N], double (*sh)[NW])
-{
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-#pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) sh[k][w] = v[k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        double s = sh[k][0];
-#pragma unroll
-        for (int u = 1; u < NW; ++u) s += sh[k][u];
-        v[k] = s;
-    }
-    __syncthreads();
+    return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // Integer combination over the workgroup: op 0 sum, 1 or, 2 min.
@@ -161,10 +167,9 @@ __device__ __forceinline__ MarkerGeo marker_geo(double bx, double by, double mx,
 // marked nodes in row-major box order, so the fields take kSlotBytes per node of the ring
 // that the supports cover next to the surface, not per node of the box.
 struct NodeView {
-    double *rho, *ux, *uy, *inv;    // density, u* (velocity with half the uniform drive and without
-                                    // the spread force), 1/rho
-    unsigned long long *fx, *fy;    // this particle's fixed-point spread force; in the probe launch
-                                    // of several particles, the total spread force (FP64 bits)
+    double *rho, *ux, *uy;          // density, u* (velocity with half the uniform drive and without
+                                    // the spread force; from forced_velocity on, with half of it)
+    unsigned long long *fx, *fy;    // this particle's fixed-point spread force
 };
 
 // A particle whose box of this step overlaps the box of the particle running the probe
@@ -176,8 +181,11 @@ struct OvEntry {
 };
 
 constexpr int kMaxParticles = 64;
-constexpr int kFields = 6;                      // per marked node: 4 doubles + 2 64-bit integers
+constexpr int kFields = 5;                      // per marked node: 3 doubles + 2 64-bit integers
 constexpr size_t kSlotBytes = kFields * 8 + 4;  // the fields and the node map entry
+constexpr size_t kScratchSlot = 52;             // global scratch of a box node
+constexpr int map_stride(int mode) { return mode == 4 ? 1 : 2; }  // of the node map, in words (phase_rest)
+constexpr size_t slot_bytes(int mode) { return mode == 4 ? kSlotBytes : kSlotBytes - 4; }
 constexpr int kFillU = 4;                       // marked nodes per lane in flight while summing forces
 constexpr size_t kLdsMax = 158 * 1024;          // dynamic LDS a workgroup may take beside the static part
 constexpr size_t kLdsHead = sizeof(OvEntry) * kMaxParticles;
@@ -189,19 +197,18 @@ size_t particle_lds_aux_bytes(int32_t box_cap)
 
 size_t particle_lds_bytes(int32_t box_cap)
 {
-    const size_t bytes = particle_lds_aux_bytes(box_cap) + (size_t)box_cap * kSlotBytes;
+    const size_t bytes = particle_lds_aux_bytes(box_cap) + (size_t)box_cap * kScratchSlot;
     return bytes <= kLdsMax ? bytes : 0;
 }
 
 size_t particle_launch_lds(int32_t box_cap)
 {
-    const size_t bytes = particle_lds_bytes(box_cap);
-    return bytes ? bytes : kLdsMax;
+    return particle_lds_bytes(box_cap) ? particle_lds_aux_bytes(box_cap) + (size_t)box_cap * kSlotBytes : kLdsMax;
 }
 
 size_t particle_scratch_bytes(int32_t box_cap)
 {
-    return particle_lds_bytes(box_cap) ? 0 : (size_t)box_cap * kSlotBytes;
+    return particle_lds_bytes(box_cap) ? 0 : (size_t)box_cap * kScratchSlot;
 }
 
 // The markers of this thread (l = threadIdx.x + k PB) at one position of the particle.
@@ -244,7 +251,7 @@ __device__ __forceinline__ void marker_set(const MarkerData<MPT>& D, int nl, int
 // Bounding box (unwrapped x) of every marker and probe support of the set: minima of
 // (i_lo, -i_hi, j_lo, -j_hi) accumulated into r[4].
 template <int MPT>
-__device__ __forceinline__ void set_bounds(const MarkerSet<MPT>& G, int ny, int (&r)[4])
+__device__ __forceinline__ void set_bounds(const MarkerSet<MPT>& G, int ny, int* r)
 {
 #pragma unroll
     for (int k = 0; k < MPT; ++k) {
@@ -330,11 +337,21 @@ __device__ __forceinline__ int mask_prefix(const uint32_t* mask, int* pre, int n
     return total;
 }
 
-// The node map: slot -> box node, for the marked nodes of mask[0..nw).  Each half-wave
-// takes one word per round, one bit per lane; four rounds' words are read at once.
+// The node map: slot -> box node, for the marked nodes of mask[0..nw), at nodes[slot STRIDE].
+// Each half-wave takes one word per round, one bit per lane; four rounds' words are read at
+// once.  A box of more words takes a word per thread, bit by bit (1113 words, 3272 marked
+// nodes: 5.2 us by half-waves).
+template <int STRIDE>
 __device__ __forceinline__ void write_node_map(const uint32_t* mask, const int* pre, int nw, int* nodes)
 {
     constexpr int kU = 4, kStep = PB / 32;
+    if (nw > 2 * kU * kStep) {
+        for (int k = threadIdx.x; k < nw; k += PB) {
+            uint32_t m = mask[k];
+            for (int s = pre[k]; m; ++s, m &= m - 1) nodes[s * STRIDE] = 32 * k + (__ffs(m) - 1);
+        }
+        return;
+    }
     const int b = threadIdx.x & 31;
     const uint32_t below = (1u << b) - 1u;
     for (int k0 = (int)(threadIdx.x >> 5); k0 < nw; k0 += kU * kStep) {
@@ -348,7 +365,7 @@ __device__ __forceinline__ void write_node_map(const uint32_t* mask, const int* 
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u)
-            if ((m[u] >> b) & 1u) nodes[p[u] + __popc(m[u] & below)] = 32 * (k0 + u * kStep) + b;
+            if ((m[u] >> b) & 1u) nodes[(p[u] + __popc(m[u] & below)) * STRIDE] = 32 * (k0 + u * kStep) + b;
     }
 }
 
@@ -412,27 +429,55 @@ constexpr int fill_nodes_per_lane(int mode)
     return St<T>::neq && mode != 1 ? 2 : 4;
 }
 
+// The velocity at a node of inverse density inv with half the spread force added.
+__device__ __forceinline__ void forced_velocity(double fx, double fy, double inv, double& ux, double& uy)
+{
+    const double hinv = 0.5 * inv;
+    ux += fx * hinv;
+    uy += fy * hinv;
+}
+
+// Row and column of box node k (k below 2^20, box width w): k / w by one multiplication with the
+// rounded reciprocal.  (k + 1/2) / w lies at least 1/(2w) from every integer, and the two
+// roundings move the product by less than 2^-22 k / w, so the truncated value is exact.
+struct BoxDiv {
+    int w;
+    float rcp;
+};
+__device__ __forceinline__ BoxDiv box_div(int w) { return BoxDiv{w, 1.0f / (float)w}; }
+__device__ __forceinline__ void box_node(const BoxDiv& d, int k, int& row, int& col)
+{
+    row = (int)(((float)k + 0.5f) * d.rcp);
+    col = k - row * d.w;
+}
+
 // Node fields at the marked nodes: slots s0 + tid + u PB for u < U per round, so the
 // loads of U nodes per lane are in flight at once and neighbouring lanes read
-// neighbouring nodes of a row.  TOTAL (the probe launch of several particles): also the
-// total spread force at each node, summed over the overlapping particles in particle order.
-template <typename T, bool TOTAL, int U>
+// neighbouring nodes of a row.  The node map is nodes[slot STRIDE]; with STRIDE 2 it lies in
+// the force field fx, each entry in its own slot.  TOTAL (the probe launch of several
+// particles): with half the total spread force at each node, summed over the overlapping
+// particles in particle order.
+template <typename T, bool TOTAL, int U, int STRIDE>
 __device__ __forceinline__ void fill_nodes(const ParticleArgs<T>& a, const NodeView& B, const int* nodes, int nm,
                                            int x0, int y0, int w, const OvEntry* ov, int nov)
 {
+    const BoxDiv bd = box_div(w);
+    const int xw = wrap(x0, a.nx);
     for (int s0 = 0; s0 < nm; s0 += PB * U) {
         int kk[U], ii[U], jj[U];
         double v[U][9];
         // A wave loads the nodes of its slots of the round where it has any (so a small box
-        // issues no loads for empty waves); a slot past the end in such a wave reads the first
-        // marked node and stores nothing, so the wave's loads carry no divergent branch.
+        // issues no loads for empty waves); a slot past the end in such a wave reads the box's
+        // first node and stores nothing, so the wave's loads carry no divergent branch.
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int sl = s0 + u * PB + (int)threadIdx.x;
-            const int k = nodes[sl < nm ? sl : 0];
-            kk[u] = sl < nm ? k : -1;
-            jj[u] = y0 + k / w;
-            ii[u] = wrap(x0 + k % w, a.nx);
+            kk[u] = sl < nm ? nodes[sl * STRIDE] : -1;
+            int row, col;
+            box_node(bd, max(kk[u], 0), row, col);
+            jj[u] = y0 + row;
+            ii[u] = xw + col;
+            if (ii[u] >= a.nx) ii[u] -= a.nx;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -496,12 +541,12 @@ __device__ __forceinline__ void fill_nodes(const ParticleArgs<T>& a, const NodeV
             shifted_moments<double, double>(v[u], dr, jx, jy);
             const double rho = 1.0 + dr;
             const double inv = 1.0 / rho;
+            double ux = (jx + 0.5 * a.gx) * inv, uy = (jy + 0.5 * a.gy) * inv;
+            if (TOTAL) forced_velocity(fx[u], fy[u], inv, ux, uy);
             B.rho[sl] = rho;
-            B.inv[sl] = inv;
-            B.ux[sl] = (jx + 0.5 * a.gx) * inv;
-            B.uy[sl] = (jy + 0.5 * a.gy) * inv;
-            B.fx[sl] = TOTAL ? (unsigned long long)__double_as_longlong(fx[u]) : 0ull;
-            B.fy[sl] = TOTAL ? (unsigned long long)__double_as_longlong(fy[u]) : 0ull;
+            B.ux[sl] = ux;
+            B.uy[sl] = uy;
+            if (!TOTAL) B.fx[sl] = B.fy[sl] = 0ull;
         }
     }
 }
@@ -522,14 +567,15 @@ __device__ __forceinline__ unsigned long long force_load(const unsigned long lon
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The total spread force at every marked node, summed over the overlapping particles in
-// particle order, written over this particle's own fixed-point value (FP64 bits): its own
-// share comes from LDS, the others' from their compact lists (the one-launch split phase,
-// after its grid barrier).
+// Adds half the total spread force at every marked node, summed over the overlapping particles
+// in particle order, to its velocity: this particle's own share comes from its node fields,
+// the others' from their compact lists (the one-launch split phase, after its grid barrier).
 template <typename T, bool LDS>
 __device__ __forceinline__ void total_forces(const ParticleArgs<T>& a, const NodeView& B, const int* nodes, int nm,
                                              int x0, int y0, int w, const OvEntry* ov, int nov)
 {
+    const BoxDiv bd = box_div(w);
+    const int xw = wrap(x0, a.nx);
     for (int s0 = 0; s0 < nm; s0 += PB * kFillU) {
         int sl[kFillU], ii[kFillU], jj[kFillU];
         double fx[kFillU], fy[kFillU];
@@ -539,9 +585,11 @@ __device__ __forceinline__ void total_forces(const ParticleArgs<T>& a, const Nod
             fx[u] = fy[u] = 0.0;
             ii[u] = jj[u] = 0;
             if (sl[u] < nm) {
-                const int k = nodes[sl[u]];
-                jj[u] = y0 + k / w;
-                ii[u] = wrap(x0 + k % w, a.nx);
+                int row, col;
+                box_node(bd, nodes[sl[u]], row, col);
+                jj[u] = y0 + row;
+                ii[u] = xw + col;
+                if (ii[u] >= a.nx) ii[u] -= a.nx;
             }
         }
         for (int e = 0; e < nov; ++e) {
@@ -582,8 +630,11 @@ __device__ __forceinline__ void total_forces(const ParticleArgs<T>& a, const Nod
 #pragma unroll
         for (int u = 0; u < kFillU; ++u) {
             if (sl[u] >= nm) continue;
-            B.fx[sl[u]] = (unsigned long long)__double_as_longlong(fx[u]);
-            B.fy[sl[u]] = (unsigned long long)__double_as_longlong(fy[u]);
+            const double inv = 1.0 / B.rho[sl[u]];
+            double ux = B.ux[sl[u]], uy = B.uy[sl[u]];
+            forced_velocity(fx[u], fy[u], inv, ux, uy);
+            B.ux[sl[u]] = ux;
+            B.uy[sl[u]] = uy;
         }
     }
 }
@@ -665,7 +716,7 @@ struct PhaseCtx {
     double xc, yc, th, ux, uy, om, cth, sth;
     double xc1, yc1, th1, ux1, uy1, om1;  // level n-1
     int64_t step;
-    int x0, y0, w, h, nbox, nmarked, flags;
+    int x0, y0, w, h, nbox, nmarked, nprobe, flags;
     bool box_ok;
     const uint32_t* mask;
     const int* pre;
@@ -675,6 +726,13 @@ struct PhaseCtx {
     TileDesc zin;
 };
 
+// The phase runs on one CU, so it is bound by the latency of its chain for small particles and
+// by that CU's memory requests and instruction issue for large ones.  us of the serial launch
+// (FP64 but where said), before -> after the node fields were cut to 40 bytes, the spread force
+// left as a list and the reductions went to register permutes: 64 markers 18.3 -> 17.1, 192
+// 19.4 -> 17.7, 576 (FP16) 43.6 -> 38.1, 960 (111 x 321 box, 3272 nodes; LDS now holds them)
+// 103 -> 41.  What is left of the last: fill 13 (its lines come from beyond the L2 at 2 ns
+// each), interpolation and probes 4 each, spread 4, list 2.
 // The particle phase after the box and its marked nodes are known; LDS: the node fields are
 // in LDS, else in the global scratch (plain loads and stores ordered by the workgroup
 // barriers, device-scope atomics for the force).
@@ -693,7 +751,8 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
     int flags = c.flags;
     DevParticle* st = a.st;
 
-    fill_nodes<T, MODE == 2, fill_nodes_per_lane<T>(MODE)>(a, B, c.nodes, c.nmarked, x0, y0, w, ov, nov);
+    fill_nodes<T, MODE == 2, fill_nodes_per_lane<T>(MODE), map_stride(MODE)>(a, B, c.nodes, c.nmarked, x0, y0, w, ov,
+                                                                             nov);
     __syncthreads();
 
     // ---- markers: MLS interpolation and direct forcing ----------------------------------
@@ -783,28 +842,31 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             }
         }
         __syncthreads();
-        if (spread_ok && (MODE == 1 || MODE == 4)) {
+        if (spread_ok) {
             // the compact list and its index for the sweep and the other particles' probes
+            // (PartRef; coherent stores in the phase of a single particle, whose concurrent sweep
+            // may read them, HandoverArgs), and, with no other particle's force to come, the
+            // velocities the probes read.  (A dense tile of the box instead, mostly zeros, took
+            // 30 us of stores for a box of 111 x 321 nodes.)
             for (int k = tid; k < c.nmarked; k += PB) {
-                longlong2 t;
-                t.x = (long long)force_load<LDS>(B.fx + k);
-                t.y = (long long)force_load<LDS>(B.fy + k);
-                *(longlong2*)(a.tile + 2 * (size_t)k) = t;
-            }
-            for (int k = tid; k < (nbox + 31) / 32; k += PB) a.ring[k] = make_uint2(mask[k], (uint32_t)pre[k]);
-        } else if (spread_ok) {
-            // the box's tile for the sweep: zero where no marker support reaches
-            for (int k = tid; k < nbox; k += PB) {
-                const uint32_t mw = mask[k >> 5];
-                unsigned long long qx = 0, qy = 0;
-                if ((mw >> (k & 31)) & 1u) {
-                    const int s = pre[k >> 5] + __popc(mw & ((1u << (k & 31)) - 1u));
-                    qx = force_load<LDS>(B.fx + s);
-                    qy = force_load<LDS>(B.fy + s);
+                const int64_t qx = (int64_t)force_load<LDS>(B.fx + k), qy = (int64_t)force_load<LDS>(B.fy + k);
+                int64_t* t = a.tile + 2 * (size_t)k;
+                if (MODE == 0) {
+                    coherent_store(t, qx);
+                    coherent_store(t + 1, qy);
+                    double ux = B.ux[k], uy = B.uy[k];
+                    forced_velocity(ldexp((double)qx, -scale), ldexp((double)qy, -scale), 1.0 / B.rho[k], ux, uy);
+                    B.ux[k] = ux;
+                    B.uy[k] = uy;
+                } else {
+                    *(longlong2*)t = longlong2{(long long)qx, (long long)qy};
                 }
-                // coherent stores: the concurrent sweep may read them (HandoverArgs)
-                coherent_store(a.tile + 2 * (size_t)k, (int64_t)qx);
-                coherent_store(a.tile + 2 * (size_t)k + 1, (int64_t)qy);
+            }
+            for (int k = tid; k < (nbox + 31) / 32; k += PB) {
+                if (MODE == 0)
+                    coherent_store((int64_t*)(a.ring + k), (int64_t)(((uint64_t)(uint32_t)pre[k] << 32) | mask[k]));
+                else
+                    a.ring[k] = make_uint2(mask[k], (uint32_t)pre[k]);
             }
         }
         if (tid == 0) {
@@ -831,6 +893,8 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             stores_done();
             __syncthreads();
             if (tid == 0) publish_counter(a.ready, a.ready_value);
+        } else if (MODE == 0) {
+            __syncthreads();  // the velocities with the spread force are complete
         }
     }
     if (MODE == 1 || MODE == 4) {
@@ -868,14 +932,12 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
 
     // ---- probe loads (eq 7-8) and wall distances ---------------------------------------
     double TX[MPT], TY[MPT], D[MPT];
-    bool PRB[MPT];
-    int nprobe = 0;
+    const int nprobe = c.nprobe;
 #pragma unroll
     for (int k = 0; k < MPT; ++k) {
         const int l = tid + k * PB;
         TX[k] = TY[k] = 0.0;
         D[k] = 0.0;
-        PRB[k] = false;
         if (l < nl) {
             Mls m;
             const bool ok = box_ok && mls_shape(c.G.PX[k], c.G.PY[k], a.ny, m, true);
@@ -889,20 +951,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
                         if (bb < m.nys && cc < m.nxs) {
                             const int e = 3 * bb + cc;
                             const int s = sr + cc;
-                            double vx = B.ux[s], vy = B.uy[s];
-                            if (MODE == 2 || MODE == 4) {
-                                const double fx = __longlong_as_double((long long)B.fx[s]);
-                                const double fy = __longlong_as_double((long long)B.fy[s]);
-                                const double hinv = 0.5 * B.inv[s];
-                                vx += fx * hinv;
-                                vy += fy * hinv;
-                            } else if (spread_ok) {
-                                const unsigned long long qx = force_load<LDS>(B.fx + s);
-                                const unsigned long long qy = force_load<LDS>(B.fy + s);
-                                const double hinv = 0.5 * B.inv[s];
-                                vx += ldexp((double)(int64_t)qx, -scale) * hinv;
-                                vy += ldexp((double)(int64_t)qy, -scale) * hinv;
-                            }
+                            const double vx = B.ux[s], vy = B.uy[s];
                             rp += m.phi[e] * B.rho[s];
                             gxx += m.psx[e] * vx;
                             gxy += m.psy[e] * vx;
@@ -920,15 +969,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
                 flags |= FLAG_MLS;
             }
             D[k] = c.G.Y[k] + 0.5;
-            PRB[k] = LIG[k] && D[k] < a.y_cr;
-            nprobe += PRB[k] ? 1 : 0;
         }
-    }
-    {
-        int v[1] = {nprobe};
-        const int op[1] = {0};
-        block_int<1>(v, op, shi);
-        nprobe = v[0];
     }
 
     // ---- bonds (eq 9-11) and the partial sums of the loads ----------------------------
@@ -1093,12 +1134,13 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     B.rho = base;
     B.ux = base + m;
     B.uy = base + 2 * m;
-    B.inv = base + 3 * m;
-    B.fx = (unsigned long long*)(base + 4 * m);
-    B.fy = (unsigned long long*)(base + 5 * m);
-    int* nodes = (int*)(base + 6 * m);
+    B.fx = (unsigned long long*)(base + 3 * m);
+    B.fy = (unsigned long long*)(base + 4 * m);
+    // the map lies in the force field, which the fill overwrites, but in MODE 4, which reads it again
+    constexpr int stride = map_stride(MODE);
+    int* nodes = stride == 2 ? (int*)B.fx : (int*)(base + 5 * m);
     c.nodes = nodes;
-    write_node_map(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
+    write_node_map<stride>(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
     __syncthreads();
     return phase_body<T, MPT, LDS, MODE>(a, c, B, ov, nov, shd, shi);
 }
@@ -1119,12 +1161,8 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
 {
     const int tid = threadIdx.x;
     OvEntry* ov = (OvEntry*)lds;
-    const int wcap = (a.box_cap + 31) / 32;
-    uint32_t* mask = (uint32_t*)(lds + kLdsHead);
-    int* pre = (int*)(mask + wcap);
-    double* fields = (double*)(pre + wcap);  // 8-byte aligned: kLdsHead and 8 wcap are multiples of 8
-    const size_t aux = kLdsHead + (size_t)wcap * 8;
-    const int lds_slots = lds_bytes > aux ? (int)((lds_bytes - aux) / kSlotBytes) : 0;
+    constexpr size_t head = MODE == 2 || MODE == 4 ? kLdsHead : 0;  // the overlap list
+    uint32_t* mask = (uint32_t*)(lds + head);
 
     // the probe launch's references to every particle's box and force list
     PartRef rq{};
@@ -1172,12 +1210,16 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     marker_set<MPT>(c.D, a.nl, a.ny, c.xc, c.yc, c.cth, c.sth, c.G);
 
     // ---- the box: every node a marker or probe support reaches this step --------------
-    int r[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
+    // (and the ligands within y_cr of the wall, which the bond draws need)
+    int r[5] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff, 0};
     set_bounds<MPT>(c.G, a.ny, r);
+#pragma unroll
+    for (int k = 0; k < MPT; ++k) r[4] += c.D.lig[k] && c.G.Y[k] + 0.5 < a.y_cr ? 1 : 0;
     {
-        const int op[4] = {2, 2, 2, 2};
-        block_int<4>(r, op, shi);
+        const int op[5] = {2, 2, 2, 2, 0};
+        block_int<5>(r, op, shi);
     }
+    c.nprobe = r[4];
     c.x0 = r[0];
     c.y0 = r[2];
     c.w = (r[0] != 0x7fffffff) ? -r[1] - r[0] + 1 : 0;
@@ -1209,6 +1251,10 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     // ---- the nodes this launch's supports reach, and their slots ------------------------
     c.nbox = c.box_ok ? c.w * c.h : 0;
     const int nw = (c.nbox + 31) / 32;
+    int* pre = (int*)(mask + nw);
+    double* fields = (double*)(pre + nw);  // 8-byte aligned: head and 8 nw are multiples of 8
+    const size_t aux = head + (size_t)nw * 8;
+    const int lds_slots = lds_bytes > aux ? (int)((lds_bytes - aux) / slot_bytes(MODE)) : 0;
     for (int k = tid; k < nw; k += PB) mask[k] = 0u;
     __syncthreads();
     if (c.box_ok)
@@ -1517,6 +1563,7 @@ __global__ __launch_bounds__(PB) void pool_particle_kernel(const ParticleArgs<T>
     a.f = buf ? a.fB : a.f;
     if (half) {
         a.tile = sims[k].tile_b;
+        a.ring = sims[k].ring_b;
         a.parity_in = 1;
         a.parity_out = 0;
         a.check_zone = 1;

@@ -264,6 +264,7 @@ lbib_status rebuild(lbib_pool* h)
         s.fA = (T*)m.fA;
         s.fB = (T*)m.fB;
         s.tile = m.p.d_tile;
+        s.ring = m.p.d_ring;
         const int by = 256 / h->cfg.bx;
         const int gx = (m.g.nx + h->cfg.bx - 1) / h->cfg.bx;
         s.gx = make_fastdiv((uint32_t)gx);
@@ -273,7 +274,7 @@ lbib_status rebuild(lbib_pool* h)
         for (int32_t t = 0; t < s.ntiles; t += h->cfg.tpb) table.push_back(make_int2((int)k, t));
         s.zone = m.p.d_zone;
         tile_off[k] = tile_elems;
-        tile_elems += 2 * (size_t)m.p.box_cap;
+        tile_elems += 2 * (size_t)m.p.box_cap + (size_t)(m.p.box_cap + 31) / 32;  // the list, then its index
         const int px = (m.g.nx + 4 * kPairStrip - 1) / (4 * kPairStrip);
         const int py = (m.g.ny + prows - 1) / prows;
         s.px = make_fastdiv((uint32_t)px);
@@ -289,7 +290,10 @@ lbib_status rebuild(lbib_pool* h)
             e = hipSuccess;
             h->pairs = false;
         }
-        for (size_t k = 0; h->pairs && k < run.size(); ++k) sims[k].tile_b = h->d_tile_b + tile_off[k];
+        for (size_t k = 0; h->pairs && k < run.size(); ++k) {
+            sims[k].tile_b = h->d_tile_b + tile_off[k];
+            sims[k].ring_b = (uint2*)(sims[k].tile_b + 2 * (size_t)run[k]->p.box_cap);
+        }
     }
     ParticleArgs<T>* dargs = (ParticleArgs<T>*)h->d_args;
     PoolSweep<T>* dsims = (PoolSweep<T>*)h->d_sims;

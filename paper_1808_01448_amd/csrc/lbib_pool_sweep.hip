@@ -12,19 +12,6 @@
 
 namespace lbib {
 
-// Adds the spread force of the dense tile of box d at node (i, j).
-__device__ __forceinline__ void tile_force(const TileDesc& d, const int64_t* __restrict__ tile, int i, int j, int nx,
-                                           double& Fx, double& Fy)
-{
-    if (d.active && in_box(d, i, j, nx)) {
-        int di = i - d.i0w;
-        if (di < 0) di += nx;
-        const int64_t* t = tile + 2 * ((size_t)(j - d.j0) * d.w + di);
-        Fx += ldexp((double)t[0], -d.scale);
-        Fy += ldexp((double)t[1], -d.scale);
-    }
-}
-
 // Sweep of a pool of independent simulations in one launch.  Block b sweeps up to TPB
 // consecutive tiles (BX x 256/BX nodes each) of member table[b].x, starting at tile
 // table[b].y; the table lists each member's tiles in order, so after the XCD remap a
@@ -63,7 +50,7 @@ __global__ __launch_bounds__(256) void pool_sweep_kernel(const PoolSweep<T>* __r
         const int j = row * BY + ty;
         if (i >= a.nx || j >= a.ny) continue;
         double Fx = a.gx, Fy = a.gy;
-        tile_force(d, ps.tile, i, j, a.nx, Fx, Fy);
+        box_force<false>(d, ps.tile, ps.ring, i, j, a.nx, Fx, Fy);
         collide_stream<T, true>(fin, fout, a, i, j, Fx, Fy);
     }
 }
@@ -125,7 +112,7 @@ __global__ __launch_bounds__(256) void pool_zone_kernel(const PoolSweep<T>* __re
         int i = z.i0w - 1 + c;
         i = i < 0 ? i + a.nx : (i >= a.nx ? i - a.nx : i);
         double Fx = a.gx, Fy = a.gy;
-        tile_force(d, ps.tile, i, j, a.nx, Fx, Fy);
+        box_force<false>(d, ps.tile, ps.ring, i, j, a.nx, Fx, Fy);
         collide_stream<T, true>(fin, fout, a, i, j, Fx, Fy);
     }
 }
@@ -144,7 +131,7 @@ __global__ __launch_bounds__(256, sizeof(typename St<T>::raw) == 8 ? 3 : 4) void
     }
     const int2 e = table[b];
     const PoolSweep<T>& ps = sims[e.x];
-    BoxForce f1{ctl[e.x], ps.tile}, f2{ctl[n_active + e.x], ps.tile_b};
+    const BoxForce f1{ctl[e.x], ps.tile, ps.ring}, f2{ctl[n_active + e.x], ps.tile_b, ps.ring_b};
     if (f1.d.pad < 0) return;
     const T* fin = f1.d.pad ? ps.fB : ps.fA;
     T* fout = f1.d.pad ? ps.fA : ps.fB;
@@ -163,7 +150,7 @@ __global__ __launch_bounds__(256, sizeof(typename St<T>::raw) == 8 ? 3 : 4) void
 #pragma unroll 1
     for (int j = r0; j < r1; ++j) {
         double Fx = a.gx, Fy = a.gy;
-        tile_force(f1.d, f1.tile, i, j, a.nx, Fx, Fy);
+        box_force<false>(f1.d, f1.tile, f1.ring, i, j, a.nx, Fx, Fy);
         collide_stream<T, true>(fin, fout, a, i, j, Fx, Fy);
     }
 }

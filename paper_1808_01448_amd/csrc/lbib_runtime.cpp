@@ -357,7 +357,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
         } else if (h->parts.empty()) {
             idle = false;
             const EvPair e0 = timing_events(h, 0);
-            HIPCHK(h, launch_sweep<T>(fin, fout, sa, nullptr, nullptr, h->g.pull, h->stream, e0.t0, e0.t1,
+            HIPCHK(h, launch_sweep<T>(fin, fout, sa, nullptr, nullptr, nullptr, h->g.pull, h->stream, e0.t0, e0.t1,
                                       reverse_sweep(h->g, h->steps)));
         } else {
             Particle& p = h->parts[0];
@@ -397,7 +397,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
                 const EvPair e1 = timing_events(h, 1);
                 HIPCHK(h, launch_particle<T>(pa, h->stream, e1.t0, e1.t1));
                 const EvPair e0 = timing_events(h, 0);
-                HIPCHK(h, launch_sweep<T>(fin, fout, sa, p.d_desc, p.d_tile, h->g.pull, h->stream, e0.t0, e0.t1,
+                HIPCHK(h, launch_sweep<T>(fin, fout, sa, p.d_desc, p.d_tile, p.d_ring, h->g.pull, h->stream, e0.t0, e0.t1,
                                           reverse_sweep(h->g, h->steps)));
                 h->zone_valid = true;
                 h->prev_overlapped = false;
@@ -431,7 +431,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
                     --run_left;
                 }
                 const HandoverArgs ha{p.d_count + 2 + 2 * (h->steps & 3), (uint32_t)(prev & 0xffffu), p.d_desc, p.d_tile,
-                                      p.d_count, prev + 1, p.d_count + 1, h->d_flags, nzone};
+                                      p.d_ring, p.d_count, prev + 1, p.d_count + 1, h->d_flags, nzone};
                 const EvPair e0 = timing_events(h, 0);
                 HIPCHK(h, launch_sweep_overlap<T>(fin, fout, sa, ha, h->g.pull, h->stream3, e0.t0, e0.t1,
                                                   reverse_sweep(h->g, h->steps)));

@@ -107,29 +107,14 @@ __device__ __forceinline__ int xcd_tile(int b, int nblocks)
     return (x < r) ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
 }
 
-// The force at node (i, j): the body force plus, inside the box d, the spread force of its
-// dense tile (COHERENT: written by a workgroup running beside this one).
-template <bool COHERENT>
-__device__ __forceinline__ void box_force(const TileDesc& d, const int64_t* __restrict__ tile, int i, int j, int nx,
-                                          double& Fx, double& Fy)
-{
-    if (d.active && in_box(d, i, j, nx)) {
-        int di = i - d.i0w;
-        if (di < 0) di += nx;
-        const int64_t* t = tile + 2 * ((size_t)(j - d.j0) * d.w + di);
-        Fx += ldexp((double)(COHERENT ? coherent_load(t) : t[0]), -d.scale);
-        Fy += ldexp((double)(COHERENT ? coherent_load(t + 1) : t[1]), -d.scale);
-    }
-}
-
-// Every node; the particle's spread force from desc / tile when desc != NULL.  rev: the tiles
+// Every node; the particle's spread force from desc / tile / ring when desc != NULL.  rev: the tiles
 // in reverse order (odd steps of a lattice well beyond the last-level cache, so that the first
 // tiles read are the last the previous sweep wrote).
 template <typename T, bool PULL>
 __global__ __launch_bounds__(256) void sweep_kernel(const T* __restrict__ fin, T* __restrict__ fout, SweepArgs a,
                                                     const TileDesc* __restrict__ desc,
-                                                    const int64_t* __restrict__ tile, FastDiv gx, int nblocks,
-                                                    int rev)
+                                                    const int64_t* __restrict__ tile,
+                                                    const uint2* __restrict__ ring, FastDiv gx, int nblocks, int rev)
 {
     using TL = Tile<PULL>;
     static_assert(TL::W >= 64, "the sweep's addressing takes each wave's nodes from one row");
@@ -140,7 +125,7 @@ __global__ __launch_bounds__(256) void sweep_kernel(const T* __restrict__ fin, T
     const int j = ty * TL::H + (int)threadIdx.x / TL::W;
     if (i >= a.nx || j >= a.ny) return;
     double Fx = a.gx, Fy = a.gy;
-    if (desc) box_force<false>(*desc, tile, i, j, a.nx, Fx, Fy);
+    if (desc) box_force<false>(*desc, tile, ring, i, j, a.nx, Fx, Fy);
     collide_stream<T, PULL>(fin, fout, a, i, j, Fx, Fy);
 }
 
@@ -200,7 +185,7 @@ __global__ __launch_bounds__(256, St<T>::neq ? 7 : 8) void sweep_overlap_kernel(
             typename St<T>::C g[9];
             update_load<T, PULL>(fin, a, i, j, g);
             double Fx = a.gx, Fy = a.gy;
-            box_force<true>(d, c.tile, i, j, a.nx, Fx, Fy);
+            box_force<true>(d, c.tile, c.ring, i, j, a.nx, Fx, Fy);
             update_store<T, PULL, true>(fout, a, i, j, g, Fx, Fy);
         }
     }
@@ -227,18 +212,7 @@ __global__ __launch_bounds__(256) void sweep_multi_kernel(const T* __restrict__ 
     double Fx = a.gx, Fy = a.gy;
     for (unsigned long long r = m; r; r &= r - 1) {
         const PartRef pr = refs[__builtin_ctzll(r)];
-        const TileDesc d = *pr.desc;
-        if (d.active && in_box(d, i, j, a.nx)) {
-            int di = i - d.i0w;
-            if (di < 0) di += a.nx;
-            const int n = (j - d.j0) * d.w + di;
-            const uint2 r = pr.ring[n >> 5];
-            if ((r.x >> (n & 31)) & 1u) {  // a marker support reaches the node
-                const int64_t* t = pr.tile + 2 * ((int)r.y + __popc(r.x & ((1u << (n & 31)) - 1u)));
-                Fx += ldexp((double)t[0], -d.scale);
-                Fy += ldexp((double)t[1], -d.scale);
-            }
-        }
+        box_force<false>(*pr.desc, pr.tile, pr.ring, i, j, a.nx, Fx, Fy);
     }
     collide_stream<T, PULL>(fin, fout, a, i, j, Fx, Fy);
 }
@@ -259,19 +233,19 @@ hipError_t launch_sweep_multi(const T* fin, T* fout, const SweepArgs& a, const u
 }
 
 template <typename T>
-hipError_t launch_sweep(const T* fin, T* fout, const SweepArgs& a, const TileDesc* desc, const int64_t* tile, bool pull,
-                        hipStream_t stream, hipEvent_t t0, hipEvent_t t1, bool rev)
+hipError_t launch_sweep(const T* fin, T* fout, const SweepArgs& a, const TileDesc* desc, const int64_t* tile,
+                        const uint2* ring, bool pull, hipStream_t stream, hipEvent_t t0, hipEvent_t t1, bool rev)
 {
     if (pull) {
         using TL = Tile<true>;
         const int gx = (a.nx + TL::W - 1) / TL::W, nb = gx * ((a.ny + TL::H - 1) / TL::H);
         hipExtLaunchKernelGGL(sweep_kernel<T, true>, dim3(nb), dim3(256), 0u, stream, t0, t1, 0u, fin, fout, a, desc,
-                              tile, make_fastdiv(gx), nb, (int)rev);
+                              tile, ring, make_fastdiv(gx), nb, (int)rev);
     } else {
         using TL = Tile<false>;
         const int gx = (a.nx + TL::W - 1) / TL::W, nb = gx * ((a.ny + TL::H - 1) / TL::H);
         hipExtLaunchKernelGGL(sweep_kernel<T, false>, dim3(nb), dim3(256), 0u, stream, t0, t1, 0u, fin, fout, a, desc,
-                              tile, make_fastdiv(gx), nb, (int)rev);
+                              tile, ring, make_fastdiv(gx), nb, (int)rev);
     }
     return hipGetLastError();
 }
@@ -298,8 +272,8 @@ hipError_t launch_sweep_overlap(const T* fin, T* fout, const SweepArgs& a, const
 #define LBIB_SWEEP_INSTANTIATE(T)                                                                               \
     template hipError_t launch_init<T>(T*, int32_t, int32_t, int32_t, int64_t, double, double, bool, int32_t,     \
                                        hipStream_t);                                                             \
-    template hipError_t launch_sweep<T>(const T*, T*, const SweepArgs&, const TileDesc*, const int64_t*, bool,     \
-                                        hipStream_t, hipEvent_t, hipEvent_t, bool);                               \
+    template hipError_t launch_sweep<T>(const T*, T*, const SweepArgs&, const TileDesc*, const int64_t*,           \
+                                        const uint2*, bool, hipStream_t, hipEvent_t, hipEvent_t, bool);                               \
     template hipError_t launch_sweep_overlap<T>(const T*, T*, const SweepArgs&, const HandoverArgs&, bool,         \
                                                 hipStream_t, hipEvent_t, hipEvent_t, bool);                       \
     template hipError_t launch_sweep_multi<T>(const T*, T*, const SweepArgs&, const unsigned long long*,           \
