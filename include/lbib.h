@@ -248,8 +248,10 @@ lbib_status lbib_load(lbib_handle h, const void* blob, int64_t size);
  * runs the particle phases of a call's overlapped steps as one launch (up to 1024 steps each)
  * whose workgroup stays on its CU from step to step; mode 1 launches the particle phase once
  * per step, and such a launch can be dispatched only once a running sweep drains, which may
- * leave it a sweep behind for the rest of the call.  Both schedules give bit-identical
- * results. */
+ * leave it a sweep behind for the rest of the call.  On lattices whose sweep moves 16 MB or more
+ * per step (and always there without particles) mode 2 sweeps two steps in one pass over memory,
+ * a call's last odd step alone; the f - f_eq storages keep one step per sweep.  All schedules
+ * give bit-identical results. */
 /* Several particles in one lattice: the particle phase is split in two halves over all
  * particles -- first every particle stages its box and spreads its marker forces, then every
  * particle evaluates its probe loads (with the spread force of every particle that reaches a
@@ -293,7 +295,8 @@ lbib_status lbib_get_layout(lbib_handle h, int32_t* pull);
 /* Kernel timing: HIP events bracket every launch of the kernels selected by the bit mask
  * `enable` (0 switches timing off): bit 0 the lattice sweep (kernel 0), bit 1 the particle
  * phase (kernel 1; in the overlapped schedule the launch includes its wait for the previous
- * sweep, and mode 2's launch over several steps counts as one launch per step), bit 2 the
+ * sweep, and mode 2's launch over several steps counts as one launch per step, as does a sweep
+ * of two), bit 2 the
  * second particle launch of the split phase (kernel 2).  lbib_kernel_time
  * synchronises and returns the summed milliseconds and launch counts since the last enable.
  * The events add work between the launches they time: time whole steps without them. */

@@ -440,77 +440,80 @@ struct Tile {
 static_assert(Tile<true>::W == Tile<false>::W && Tile<true>::H == Tile<false>::H,
               "the particle phase predicts the box's tiles for either layout");
 
-// The TW x TH node tiles of the sweep that a box, widened by m nodes on every side, reaches:
-// columns tx0, tx0 + 1, ... (ntx of them, periodic over the gx columns; the last column may be
-// narrower than TW nodes), rows ty0 .. ty0 + nty - 1.  Zone tile e is column
-// (tx0 + e % ntx) mod gx of row ty0 + e / ntx.  The box is inactive, or has i0w in [0, nx),
-// w <= nx and rows j0 .. j0 + h - 1 in [0, ny).
-struct ZoneTiles {
-    int tx0, ntx, ty0, nty;
+// A box of the particle widened by m nodes on every side, cut at the walls: columns i0, i0 + 1,
+// ... (w of them, periodic), rows j0 .. j0 + h - 1.  No nodes (w = 0) for an inactive box; an
+// active one has i0w in [0, nx), w <= nx and rows in [0, ny).
+struct Zone {
+    int i0, w, j0, h;
 };
-template <int TW, int TH>
-__device__ __forceinline__ ZoneTiles zone_tiles(const TileDesc& z, int nx, int ny, int gx, int m)
+__device__ __forceinline__ Zone widened(const TileDesc& z, int nx, int ny, int m)
 {
-    ZoneTiles t{0, 0, 0, 0};
-    if (!z.active || z.w <= 0 || z.h <= 0) return t;
-    const int w = min(z.w + 2 * m, nx);
-    int i0 = z.i0w - m;
-    if (i0 < 0) i0 += nx;
-    t.tx0 = i0 / TW;
-    int covered = min(TW * t.tx0 + TW, nx) - i0;
-    int tx = t.tx0;
-    t.ntx = 1;
-    while (covered < w && t.ntx < gx) {
-        tx = tx + 1 == gx ? 0 : tx + 1;
-        covered += min(TW * tx + TW, nx) - TW * tx;
-        ++t.ntx;
-    }
-    t.ty0 = max(z.j0 - m, 0) / TH;
-    t.nty = min(z.j0 + z.h - 1 + m, ny - 1) / TH - t.ty0 + 1;
-    return t;
+    if (!z.active || z.w <= 0 || z.h <= 0) return Zone{0, 0, 0, 0};
+    Zone r;
+    r.w = min(z.w + 2 * m, nx);
+    r.i0 = z.i0w - m;
+    if (r.i0 < 0) r.i0 += nx;
+    r.j0 = max(z.j0 - m, 0);
+    r.h = min(z.j0 + z.h - 1 + m, ny - 1) - r.j0 + 1;
+    return r;
 }
-__device__ __forceinline__ bool zone_has_tile(const ZoneTiles& t, int tx, int ty, int gx)
+// The columns of cells W nodes wide (g of them, the last perhaps narrower) that the zone reaches:
+// c0, c0 + 1, ... (n of them, periodic over g).
+struct ZoneCols {
+    int c0, n;
+};
+template <int W>
+__device__ __forceinline__ ZoneCols zone_cols(const Zone& z, int nx, int g)
 {
-    if (ty < t.ty0 || ty >= t.ty0 + t.nty) return false;
-    int k = tx - t.tx0;
-    if (k < 0) k += gx;
-    return k < t.ntx;
+    ZoneCols c{z.i0 / W, 0};
+    if (z.w <= 0) return c;
+    const int end = z.i0 + z.w - 1;
+    c.n = min(end < nx ? end / W - c.c0 + 1 : g - c.c0 + (end - nx) / W + 1, g);
+    return c;
+}
+__device__ __forceinline__ bool has_col(const ZoneCols& c, int k, int g)
+{
+    k -= c.c0;
+    if (k < 0) k += g;
+    return k < c.n;
 }
 
-// The sweep tiles of a predicted box (zone_tiles) in two 64-bit words, each carrying a 16-bit
-// tag, so that one coherent load of each gives a consistent value (both tags current) without
-// a separate flag: word 0 tx0 (24 bits), ty0 (24); word 1 ntx (24), nty (23); tag in the top
-// 16 bits of both.  Needs gx < 2^24 and ny < 2^23 (no tiles otherwise).
-__device__ __forceinline__ void zone_pack(const ZoneTiles& z, uint32_t tag, unsigned long long* p)
+// The widened box of a prediction in two 64-bit words, each carrying a 16-bit tag, so that one
+// coherent load of each gives a consistent value (both tags current) without a separate flag:
+// word 0 the low 24 bits of i0, j0 (24); word 1 w (12), h (12), the high 8 bits of i0; tag in
+// the top 16 bits of both.  A box has at most 10^6 nodes in a square, so w and h stay far below
+// 2^12; j0 below 2^24 (no nodes otherwise).
+__device__ __forceinline__ void zone_pack(const Zone& z, uint32_t tag, unsigned long long* p)
 {
     const unsigned long long t = (unsigned long long)(tag & 0xffffu) << 48;
-    const bool ok = z.ntx > 0 && z.nty > 0 && z.tx0 < (1 << 24) && z.ntx < (1 << 24) && z.ty0 < (1 << 24) &&
-                    z.nty < (1 << 23);
-    const unsigned long long w0 = ok ? ((unsigned long long)z.ty0 << 24) | (unsigned long long)z.tx0 : 0ull;
-    const unsigned long long w1 = ok ? ((unsigned long long)z.nty << 24) | (unsigned long long)z.ntx : 0ull;
+    const bool ok = z.w > 0 && z.h > 0 && z.w < (1 << 12) && z.h < (1 << 12) && z.j0 < (1 << 24);
+    const unsigned long long i0 = (unsigned)z.i0;
+    const unsigned long long w0 = ok ? ((unsigned long long)z.j0 << 24) | (i0 & 0xffffffu) : 0ull;
+    const unsigned long long w1 =
+        ok ? ((i0 >> 24) << 24) | ((unsigned long long)z.h << 12) | (unsigned long long)z.w : 0ull;
     coherent_store((int64_t*)p, (int64_t)(t | w0));
     coherent_store((int64_t*)p + 1, (int64_t)(t | w1));
 }
-__device__ __forceinline__ ZoneTiles zone_unpack(unsigned long long w0, unsigned long long w1)
+__device__ __forceinline__ Zone zone_unpack(unsigned long long w0, unsigned long long w1)
 {
-    return ZoneTiles{(int)(w0 & 0xffffffu), (int)(w1 & 0xffffffu), (int)((w0 >> 24) & 0xffffffu),
-                     (int)((w1 >> 24) & 0x7fffffu)};
+    return Zone{(int)((w0 & 0xffffffu) | (w1 & 0xff000000u)), (int)(w1 & 0xfffu), (int)((w0 >> 24) & 0xffffffu),
+                (int)((w1 >> 12) & 0xfffu)};
 }
-// Waits (one lane) until both words carry tag, then unpacks them (no tiles when the wait
+// Waits (one lane) until both words carry tag, then unpacks them (no nodes when the wait
 // times out, which raises FLAG_SYNC).  The first attempt uses plain loads: the tags validate
 // whatever they return (a stale copy only carries an older tag), and once the words are
 // written they mostly hit in the L2 that the first workgroup of the XCD filled.
-__device__ __forceinline__ ZoneTiles zone_wait(const unsigned long long* p, uint32_t tag, int32_t* flags)
+__device__ __forceinline__ Zone zone_wait(const unsigned long long* p, uint32_t tag, int32_t* flags)
 {
     const unsigned long long t = tag & 0xffffu;
     unsigned long long w0 = p[0], w1 = p[1];
     for (unsigned polls = 0;; ++polls) {
         if ((w0 >> 48) == t && (w1 >> 48) == t) return zone_unpack(w0, w1);
         if ((polls & 255u) == 0 && (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & FLAG_SYNC))
-            return ZoneTiles{0, 0, 0, 0};
+            return Zone{0, 0, 0, 0};
         if (polls > (1u << 20)) {
             atomicOr(flags, FLAG_SYNC);
-            return ZoneTiles{0, 0, 0, 0};
+            return Zone{0, 0, 0, 0};
         }
         if (polls) __builtin_amdgcn_s_sleep(1);
         w0 = (unsigned long long)coherent_load((const int64_t*)p);
@@ -525,7 +528,7 @@ __device__ __forceinline__ unsigned long long first_lane(unsigned long long v)
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
     return ((unsigned long long)hi << 32) | lo;
 }
-__device__ __forceinline__ ZoneTiles zone_wait_wave(const unsigned long long* p, uint32_t tag, int32_t* flags)
+__device__ __forceinline__ Zone zone_wait_wave(const unsigned long long* p, uint32_t tag, int32_t* flags)
 {
     const unsigned long long t = tag & 0xffffu;
     unsigned long long w0 = first_lane(p[0]), w1 = first_lane(p[1]);
@@ -534,10 +537,10 @@ __device__ __forceinline__ ZoneTiles zone_wait_wave(const unsigned long long* p,
         if ((polls & 255u) == 0 &&
             (__builtin_amdgcn_readfirstlane(__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) &
              FLAG_SYNC))
-            return ZoneTiles{0, 0, 0, 0};
+            return Zone{0, 0, 0, 0};
         if (polls > (1u << 20)) {
             if (__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) == 0) atomicOr(flags, FLAG_SYNC);
-            return ZoneTiles{0, 0, 0, 0};
+            return Zone{0, 0, 0, 0};
         }
         if (polls) __builtin_amdgcn_s_sleep(1);
         w0 = first_lane((unsigned long long)coherent_load((const int64_t*)p));

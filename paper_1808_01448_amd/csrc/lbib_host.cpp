@@ -197,13 +197,48 @@ int zone_workgroups(const Particle& p, bool pull)
     return std::min(64, (((zs + tw - 1) / tw + 1) * ((zs + th - 1) / th + 1) + 7) / 8 * 8);
 }
 
+// The two-step sweep's: one for each four rows of the units (four strips by `rows` rows) that the
+// widened box can reach, at most 64.
+int pair_zone_workgroups(const Particle& p, int rows)
+{
+    const int unit = 4 * kPairStrip, zs = p.zone_side;
+    const int cols = (zs + unit - 2) / unit + 1, units = (zs + rows - 2) / rows + 1;
+    return std::min(64, (cols * units * ((rows + 3) / 4) + 7) / 8 * 8);
+}
+
+// Whether a simulation's sweeps take two steps in one pass over memory (PairHandover): from
+// kPairBytes of traffic per step, and where a window of three rows fits a buffer resource's
+// bound.  us per step, one step per sweep -> two, with a particle / without: 2.4 MB (256 x 64
+// FP64) 17.3 -> 17.3 / 2.9 -> 2.9 and calls of 6 steps 22.3 -> 22.9 / 4.8 -> 4.9; 9.4 MB 19.0 ->
+// 18.5 / 3.3 -> 3.1, 6-step calls 23.9 -> 24.3; 19 MB (1024 x 256 FP32) 20.9 -> 19.2 / 4.5 ->
+// 4.4; 58 MB (2000 x 200 FP64) 21.7 -> 19.7 / 9.9 -> 6.1; 302 MB (4096 x 1024 FP32) 44.2 -> 35.3 /
+// 42.9 -> 32.7; 2.4 GB 399 -> 280; FP64 604 MB 95 -> 75 (a 960-marker particle), FP16 1.2 GB 204 ->
+// 154.  Below, short calls lose as much as long ones gain.  Not the f - f_eq storages: their
+// sweep is not bound by traffic.
+bool pair_sweeps(const LatticeGeom& g)
+{
+    constexpr double kPairBytes = 16e6;
+    return !g.neq && 3 * (int64_t)g.pitch * (int64_t)g.elem < (int64_t)1 << 31 &&
+           (double)g.upd_bytes * g.nx * g.ny >= kPairBytes;
+}
+// Rows of a unit.  Alone, enough units to fill the GPU: a wave's rows go one after the other (4
+// rows 6.1, 8 6.0, 16 7.7 us per step on 2000 x 200 FP64; 1500 x 384 FP32 6.1, 6.8, 7.5; 4096 x
+// 1024 FP32 8 rows 32.7, 16 33.8; beyond 2^23 nodes 16 rows 276, 8 288).  Beside a particle the
+// fewest waves that keep up are best, which leave its phase the memory system (8 rows 35.8, 12
+// 34.8, 16 35.3, 24 37.1 us at 4096 x 1024 FP32; 2000 x 200 FP64 20.2, -, 19.7).
+int pair_rows(const LatticeGeom& g, bool particle)
+{
+    const int64_t nodes = (int64_t)g.nx * g.ny;
+    return particle || nodes >= (int64_t)1 << 23 ? 16 : nodes >= (int64_t)1 << 20 ? 8 : 4;
+}
+
 size_t particle_block_bytes(const Particle& p)
 {
     const size_t nl = (size_t)p.nl, cap = (size_t)p.box_cap;
     const size_t scratch = particle_scratch_bytes(p.box_cap);
     return 2 * align_up(2 * nl * 8) + align_up(nl * 8) + 2 * align_up(nl) + align_up(2 * cap * 8) +
            align_up((cap + 31) / 32 * 8) + (scratch ? align_up(scratch) : 0) + align_up(sizeof(TileDesc)) +
-           align_up(2 * sizeof(TileDesc)) + align_up(16 * 8) + align_up(sizeof(DevParticle));
+           align_up(3 * sizeof(TileDesc)) + align_up(16 * 8) + align_up(sizeof(DevParticle));
 }
 
 void carve_particle(Particle& p, char* block)
@@ -225,7 +260,7 @@ void carve_particle(Particle& p, char* block)
     const size_t scratch = particle_scratch_bytes(p.box_cap);
     p.d_box = scratch ? (double*)take(scratch) : nullptr;
     p.d_desc = (TileDesc*)take(sizeof(TileDesc));
-    p.d_zone = (TileDesc*)take(2 * sizeof(TileDesc));
+    p.d_zone = (TileDesc*)take(3 * sizeof(TileDesc));
     p.d_count = (unsigned long long*)take(16 * 8);
     p.d_st = (DevParticle*)take(sizeof(DevParticle));
     p.block = block;

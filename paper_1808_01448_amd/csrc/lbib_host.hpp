@@ -61,7 +61,7 @@ struct Particle {
     double* d_box = nullptr;  // node fields and node map when they may not fit in LDS
     int box_cap = 0;
     TileDesc* d_desc = nullptr;
-    TileDesc* d_zone = nullptr;  // two slots, by step parity
+    TileDesc* d_zone = nullptr;  // two slots, by step parity; a third for the first of two steps
     // the overlapped schedule's hand-over words (0: force-ready count, 1: zone workgroups'
     // count, from 2: four slots of the packed box; ParticleArgs, HandoverArgs) and the side of
     // its widened box at most
@@ -119,6 +119,9 @@ inline size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
 
 // Bytes of the particle's device block (every buffer aligned to 256 bytes).
 int zone_workgroups(const Particle& p, bool pull);
+int pair_zone_workgroups(const Particle& p, int rows);
+bool pair_sweeps(const LatticeGeom& g);
+int pair_rows(const LatticeGeom& g, bool particle);  // rows of a unit of the two-step sweep
 size_t particle_block_bytes(const Particle& p);
 // Point the particle's buffers into `block` (particle_block_bytes(p) bytes, not owned).
 void carve_particle(Particle& p, char* block);

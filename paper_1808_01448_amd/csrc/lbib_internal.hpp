@@ -207,8 +207,8 @@ struct ParticleArgs {
     int32_t mtx;
     int32_t nparts;  // entries of refs
     // hand-over of the overlapped schedule (NULL: none): once its tile and desc have completed
-    // the particle stores ready_value into the monotonic counter *ready; the sweep tiles of
-    // its prediction of the next box go to the two words at zone_words, packed with zone_tag
+    // the particle stores ready_value into the monotonic counter *ready; its prediction of the
+    // next box, widened, goes to the two words at zone_words, packed with zone_tag
     // (zone_pack), after its last read of f
     unsigned long long* ready;
     unsigned long long ready_value;
@@ -218,9 +218,13 @@ struct ParticleArgs {
     // (the previous sweep's zone workgroups have stored their results; NULL: no wait), and
     // with check_prev checks that its box lies inside the box zone[parity_out] (the previous
     // step's), widened by kZoneMargin - 1
+    // and in check_prev 2 (the first of two steps after another two swept together) that it lies
+    // so inside the box zone[2], that of the step before the previous one, which such a first
+    // step (pair_first) leaves there
     unsigned long long* zdone;
     unsigned long long zdone_target;
     int32_t check_prev;
+    int32_t pair_first;
     // the one-launch split phase: grid-barrier counter and the value this launch waits for
     unsigned long long* bar;
     unsigned long long bar_target;
@@ -233,8 +237,8 @@ template <typename T>
 hipError_t launch_init(T* f, int32_t nx, int32_t ny, int32_t pitch, int64_t plane, double umax, double scale,
                        bool pull, int32_t drive, hipStream_t stream);
 // The sweep beside the particle phase of one particle (the overlapped schedule), on its own
-// stream with no event between it and the particle's launches.  Every wave reads the sweep
-// tiles of this step's box as the previous particle launch predicted it (zone_words, two
+// stream with no event between it and the particle's launches.  Every wave reads this step's
+// box, widened, as the previous particle launch predicted it (zone_words, two
 // words that carry zone_tag when that launch wrote them; it wrote them after its last read
 // of the buffer this sweep overwrites), waiting until the tags match.  The workgroups of the lattice skip every
 // node tile the box reaches; nzone more workgroups (a multiple of 8, at most 64), before them
@@ -264,6 +268,24 @@ struct HandoverArgs {
 template <typename T>
 hipError_t launch_sweep_overlap(const T* fin, T* fout, const SweepArgs& a, const HandoverArgs& c, bool pull,
                                 hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr, bool rev = false);
+// Two steps (n, n+1) in one pass over memory (march_pair), beside the particle phase of one
+// particle, or of a lattice without particles (c.nzone 0).  A unit is four strips of kPairStrip
+// columns by `rows` rows, a workgroup each.  The first nzone workgroups take the units that
+// the box of step n reaches, widened by kZoneMargin nodes (as step n's zone words give it):
+// they first sweep step n at the nodes of that widened box into the other buffer,
+// once the particle has published its force of step n, and count in at *zdone, which releases
+// the particle's step n+1; once its force is published too they run both steps of their units,
+// overwriting the zone, and count in again.  The other workgroups run the other units, which
+// no force reaches.  Same waits and bounds as the one-step sweep.  Not for the f - f_eq storages.
+struct PairHandover {
+    HandoverArgs h;  // step n: words, box, force, ready count
+    const TileDesc* desc_b;  // step n+1
+    const int64_t* tile_b;
+    const uint2* ring_b;
+};
+template <typename T>
+hipError_t launch_sweep_pair(const T* fin, T* fout, const SweepArgs& a, const PairHandover& c, int32_t rows, bool pull,
+                             hipStream_t stream, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr, bool rev = false);
 // Sweep of a step with several particles: node forces from every particle whose box reaches
 // the node (listed by the tile mask mcur, summed in particle order); each block also clears
 // its tile's word of mnext, the mask of the next step.
@@ -300,6 +322,10 @@ hipError_t launch_particle(const ParticleArgs<T>& a, hipStream_t stream, hipEven
 // its box slots are (step0 + k) mod 2, its ready value and zone tag advance by k, its zone
 // words are the pair at zone_base + 2 ((step0 + k + 1) mod 4), the count it waits for advances
 // by k nzone, and every step after the first checks its box against the previous one.
+// pairs: the sweeps take the run's steps two at a time (a last odd one alone): the first of two
+// reads the level the last sweep left, the second its zone in the buffer that sweep will
+// overwrite (so the buffers of four steps are even, odd, odd, even), and leaves its force in
+// tile_b, ring_b and desc_b.
 template <typename T>
 struct ParticleRun {
     const T* f_even;
@@ -308,6 +334,10 @@ struct ParticleRun {
     int64_t step0;
     int32_t nsteps;
     int32_t nzone;
+    int32_t pairs;
+    int64_t* tile_b;
+    uint2* ring_b;
+    TileDesc* desc_b;
 };
 template <typename T>
 hipError_t launch_particle_run(const ParticleArgs<T>& a, const ParticleRun<T>& run, hipStream_t stream,

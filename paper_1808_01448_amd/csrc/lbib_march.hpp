@@ -121,16 +121,18 @@ __device__ __forceinline__ S window_load(__amdgpu_buffer_rsrc_t w, uint32_t v, u
     else
         return __builtin_bit_cast(S, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(w, v, s, 0));
 }
-template <typename V>
+// COH: visible to other XCDs without cache maintenance (sc1, as the agent-scope stores).
+template <bool COH, typename V>
 __device__ __forceinline__ void window_store(__amdgpu_buffer_rsrc_t w, uint32_t v, uint32_t s, V x)
 {
+    constexpr int aux = COH ? 16 : 0;
     if constexpr (sizeof(V) == 8) {
         typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), w, v, s, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), w, v, s, aux);
     } else if constexpr (sizeof(V) == 4) {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), w, v, s, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), w, v, s, aux);
     } else {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, x), w, v, s, 0);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, x), w, v, s, aux);
     }
 }
 
@@ -149,7 +151,8 @@ __device__ __forceinline__ void row_load(const T* __restrict__ fin, const SweepA
         if (PULL && kEy[q] != 0) {
             const bool wall = kEy[q] > 0 ? bot : top;
             s = wall ? R + kOpp[q] * P : (uint32_t)(1 - kEy[q]) * R + q * P;
-            o = kEx[q] == 0 ? c.o[1] : (wall ? c.o[1] : c.o[1 - kEx[q]]);
+            const uint32_t own = c.o[1], from = c.o[1 - kEx[q]];
+            o = wall ? own : from;
         } else if (PULL) {
             o = c.o[1 - kEx[q]];
         }
@@ -159,7 +162,7 @@ __device__ __forceinline__ void row_load(const T* __restrict__ fin, const SweepA
 
 // The results of row j: at the node itself (pull) or scattered to the neighbours (push), as
 // pull_store and push_store do.  c: the lane's columns, or kNoStore.
-template <typename T, bool PULL>
+template <typename T, bool PULL, bool COH>
 __device__ __forceinline__ void row_store(T* __restrict__ fout, const SweepArgs& a, const Cols& c, int j,
                                           const typename St<T>::C (&post)[9])
 {
@@ -174,11 +177,12 @@ __device__ __forceinline__ void row_store(T* __restrict__ fout, const SweepArgs&
         if (!PULL && kEy[q] != 0) {
             const bool wall = kEy[q] > 0 ? top : bot;
             s = wall ? R + kOpp[q] * P : (uint32_t)(1 + kEy[q]) * R + q * P;
-            o = kEx[q] == 0 ? c.o[1] : (wall ? c.o[1] : c.o[1 + kEx[q]]);
+            const uint32_t own = c.o[1], out = c.o[1 + kEx[q]];
+            o = wall ? own : out;
         } else if (!PULL) {
             o = c.o[1 + kEx[q]];
         }
-        window_store<S>(w, o, s, keep_value(tag, post[q], a));
+        window_store<COH, S>(w, o, s, keep_value(tag, post[q], a));
     }
 }
 
@@ -188,7 +192,9 @@ __device__ __forceinline__ void row_store(T* __restrict__ fout, const SweepArgs&
 // neighbours.  f1, f2: the spread forces of step n and n+1.  A row's loads are issued two rows
 // ahead, into the registers of the row being worked on.  Every wave of the workgroup that calls
 // this works on the same rows (it meets the others in a workgroup barrier every second row).
-template <typename T, bool PULL>
+// COH: the forces come from a launch running beside this one, and such a launch reads the
+// results.
+template <typename T, bool PULL, bool COH = false>
 __device__ __forceinline__ void march_pair(const T* __restrict__ fin, T* __restrict__ fout, const SweepArgs& a, int c0,
                                            int r0, int r1, const BoxForce& f1, const BoxForce& f2)
 {
@@ -210,7 +216,7 @@ __device__ __forceinline__ void march_pair(const T* __restrict__ fin, T* __restr
     const bool any1 = col_in(f1.d), any2 = col_in(f2.d);
     auto force = [&](const BoxForce& f, bool any, int j, C& Fx, C& Fy) {
         double x = a.gx, y = a.gy;
-        if (any && j >= f.d.j0 && j < f.d.j0 + f.d.h) box_force<false>(f.d, f.tile, f.ring, i, j, a.nx, x, y);
+        if (any && j >= f.d.j0 && j < f.d.j0 + f.d.h) box_force<COH>(f.d, f.tile, f.ring, i, j, a.nx, x, y);
         Fx = (C)x;
         Fy = (C)y;
     };
@@ -256,7 +262,7 @@ __device__ __forceinline__ void march_pair(const T* __restrict__ fin, T* __restr
         wall_reflect<C>(g, j, a.ny, a.uw6);
         force(f2, any2, j, Fx, Fy);
         collide_node<C>(g, a, Fx, Fy, post);
-        row_store<T, PULL>(fout, a, cs, j, post);
+        row_store<T, PULL, COH>(fout, a, cs, j, post);
     };
     V ev[9], od[9];
     row_load<T, PULL>(fin, a, c, ra, ev);

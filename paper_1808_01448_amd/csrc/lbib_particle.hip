@@ -880,6 +880,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             d.i0u = box_ok ? x0 : 0;
             d.pad = 0;
             coherent_store(a.desc, d);
+            if (MODE == 0 && a.pair_first) a.zone[2] = d;
             if (a.check_zone) {
                 const TileDesc z = c.zin;
                 // the concurrent sweep sweeps the tiles of the predicted box with this force:
@@ -1113,11 +1114,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             a.zone[a.parity_out] = z;
             // the next sweep reads the box from these words, and overwrites f once it has
             // them: f was last read by the probes, whose results the update above used
-            if (a.zone_words) {
-                using TL = Tile<false>;
-                const int gx = (a.nx + TL::W - 1) / TL::W;
-                zone_pack(zone_tiles<TL::W, TL::H>(z, a.nx, a.ny, gx, kZoneMargin), a.zone_tag, a.zone_words);
-            }
+            if (a.zone_words) zone_pack(widened(z, a.nx, a.ny, kZoneMargin), a.zone_tag, a.zone_words);
         }
     }
     return true;
@@ -1234,9 +1231,10 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
             wait_counter(a.zdone, a.zdone_target, a.flags);
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             if (a.check_prev && c.box_ok) {
-                // those workgroups covered the previous box widened by kZoneMargin: this box
-                // must lie in it widened by kZoneMargin - 1 (its readers' sources one further)
-                const TileDesc zp = a.zone[a.parity_out];
+                // those workgroups covered the previous box (of the last two steps swept together,
+                // the first's) widened by kZoneMargin: this box must lie in it widened by
+                // kZoneMargin - 1 (its readers' sources one further)
+                const TileDesc zp = a.zone[a.check_prev == 2 ? 2 : a.parity_out];
                 const int m = kZoneMargin - 1;
                 int dx = ((c.x0 - zp.i0w) % a.nx + a.nx) % a.nx;
                 if (dx >= a.nx / 2) dx -= a.nx;
@@ -1331,14 +1329,21 @@ __device__ __noinline__ void run_step(int32_t k_in)
     const ParticleRun<T> run = sg.run;
     const uint32_t lds_bytes = sg.lds_bytes;
     const int64_t step = run.step0 + k;
-    a.f = (k & 1) ? run.f_odd : run.f_even;
+    const bool second = run.pairs && (k & 1);
+    a.f = ((run.pairs ? (k + 1) >> 1 : k) & 1) ? run.f_odd : run.f_even;
+    a.pair_first = run.pairs && !second;
+    if (second) {
+        a.tile = run.tile_b;
+        a.ring = run.ring_b;
+        a.desc = run.desc_b;
+    }
     a.parity_in = (int32_t)(step & 1);
     a.parity_out = a.parity_in ^ 1;
     a.ready_value += (unsigned long long)k;
     a.zone_words = run.zone_base + 2 * ((step + 1) & 3);
     a.zone_tag = (uint32_t)(a.ready_value & 0xffffu);
     a.zdone_target += (unsigned long long)k * (unsigned long long)run.nzone;
-    if (k > 0) a.check_prev = 1;
+    if (k > 0) a.check_prev = a.pair_first ? 2 : 1;
     particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes);
 }
 
@@ -1644,7 +1649,8 @@ template <typename T>
 hipError_t launch_particle_run(const ParticleArgs<T>& a, const ParticleRun<T>& run, hipStream_t stream, hipEvent_t t0,
                                hipEvent_t t1)
 {
-    if (run.nsteps <= 0 || !run.f_even || !run.f_odd || !run.zone_base || !a.ready || !a.zdone || !a.check_zone)
+    if (run.nsteps <= 0 || !run.f_even || !run.f_odd || !run.zone_base || !a.ready || !a.zdone || !a.check_zone ||
+        (run.pairs && (!run.tile_b || !run.ring_b || !run.desc_b)))
         return hipErrorInvalidValue;
     if (a.nl <= PB) return launch_particle_run_mpt<T, 1>(a, run, stream, t0, t1);
     if (a.nl <= 2 * PB) return launch_particle_run_mpt<T, 2>(a, run, stream, t0, t1);

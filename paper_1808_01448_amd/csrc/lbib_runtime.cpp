@@ -46,6 +46,13 @@ struct lbib_sim {
     unsigned long long plaunches = 0;  // single-particle launches since lbib_init (hand-over counts)
     unsigned long long zdone_expected = 0;  // zone workgroups of the overlapped sweeps enqueued
     bool prev_overlapped = false;           // the last step enqueued ran overlapped
+    bool prev_pair = false;                 // and was the second of two swept together
+    // two steps per sweep (PairHandover): the second step's force list, its index and its box
+    bool pairs = false;
+    char* d_pair = nullptr;
+    int64_t* d_tile_b = nullptr;
+    uint2* d_ring_b = nullptr;
+    TileDesc* d_desc_b = nullptr;
     hipEvent_t evA = nullptr, evB = nullptr, evC = nullptr;
     int overlap = 2;  // 0 serial, 1 overlapped, 2 chosen by lattice size, 3 split particle phase, 4 one-launch split phase
     int layout = 2;   // 0 push, 1 pull, 2 chosen by lattice size (at lbib_init)
@@ -154,6 +161,8 @@ void free_all(lbib_sim* h)
     h->ev_end = nullptr;
     dfree(h->stage.p);
     h->stage.bytes = 0;
+    dfree(h->d_pair);
+    h->pairs = false;
     dfree(h->d_masks);
     dfree(h->d_bar);
     dfree(h->d_refs);
@@ -265,7 +274,8 @@ hipError_t ensure_sweep_stream(lbib_sim* h)
     return hipStreamCreateWithFlags(&h->stream3, hipStreamNonBlocking);
 }
 
-// One time step is the particle phase then the lattice sweep.  Serial schedule: both on the
+// One time step is the particle phase then the lattice sweep; mode 2 of a large lattice, and a
+// lattice without particles, sweep two steps in one pass over memory (PairHandover).  Serial schedule: both on the
 // caller's stream.  Overlapped schedule (when the previous step has predicted this step's
 // box): the particle phase runs on the second stream while the caller's stream sweeps the
 // lattice on a third, with no event between the two chains but the particle's wait for the
@@ -292,6 +302,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
     for (int64_t s = 0; s < n; ++s) {
         const T* fin = (const T*)h->fA;
         T* fout = (T*)h->fB;
+        int took = 1;  // steps of this pass
         if (split) {
             // every particle spreads and marks the tile mask, then every particle evaluates its
             // loads (seeing all spread forces) and moves, then the lattice is swept
@@ -354,6 +365,12 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
             const EvPair e0 = timing_events(h, 0);
             HIPCHK(h, launch_sweep_multi<T>(fin, fout, sa, mcur, mnext, h->d_refs, h->g.pull, h->stream, e0.t0, e0.t1));
             h->zone_valid = false;
+        } else if (h->parts.empty() && h->pairs && n - s >= 2) {
+            idle = false;
+            const EvPair e0 = timing_events(h, 0, 2);
+            HIPCHK(h, launch_sweep_pair<T>(fin, fout, sa, PairHandover{}, pair_rows(h->g, false), h->g.pull, h->stream, e0.t0,
+                                           e0.t1, reverse_sweep(h->g, h->steps / 2)));
+            took = 2;
         } else if (h->parts.empty()) {
             idle = false;
             const EvPair e0 = timing_events(h, 0);
@@ -413,8 +430,11 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
                 pa.check_zone = 1;
                 pa.zdone = p.d_count + 1;
                 pa.zdone_target = h->zdone_expected;
-                pa.check_prev = h->prev_overlapped ? 1 : 0;
-                const int nzone = zone_workgroups(p, h->g.pull);
+                pa.check_prev = !h->prev_overlapped ? 0 : h->prev_pair ? 2 : 1;
+                // mode 2 of a large lattice: two steps per sweep, a last odd step alone
+                const bool pairs = h->overlap == 2 && h->pairs;
+                const int rows = pair_rows(h->g, true);
+                const int nzone = pairs ? pair_zone_workgroups(p, rows) : zone_workgroups(p, h->g.pull);
                 if (h->overlap == 1) {  // a launch per step
                     const EvPair e1 = timing_events(h, 1);
                     HIPCHK(h, launch_particle<T>(pa, h->stream2, e1.t0, e1.t1));
@@ -423,25 +443,36 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
                     // step of the call is overlapped too), its workgroup resident between them
                     if (run_left == 0) {
                         const int64_t len = std::min<int64_t>(n - s, kRunSteps);
-                        const ParticleRun<T> run{fin, (const T*)h->fB, p.d_count + 2, h->steps, (int32_t)len, nzone};
+                        const ParticleRun<T> run{fin,   (const T*)h->fB, p.d_count + 2, h->steps,    (int32_t)len,
+                                                 nzone, pairs ? 1 : 0,   h->d_tile_b,   h->d_ring_b, h->d_desc_b};
                         const EvPair e1 = timing_events(h, 1, len);
                         HIPCHK(h, launch_particle_run<T>(pa, run, h->stream2, e1.t0, e1.t1));
                         run_left = len;
                     }
-                    --run_left;
+                    if (pairs && run_left >= 2) took = 2;
+                    run_left -= took;
                 }
                 const HandoverArgs ha{p.d_count + 2 + 2 * (h->steps & 3), (uint32_t)(prev & 0xffffu), p.d_desc, p.d_tile,
                                       p.d_ring, p.d_count, prev + 1, p.d_count + 1, h->d_flags, nzone};
-                const EvPair e0 = timing_events(h, 0);
-                HIPCHK(h, launch_sweep_overlap<T>(fin, fout, sa, ha, h->g.pull, h->stream3, e0.t0, e0.t1,
-                                                  reverse_sweep(h->g, h->steps)));
-                h->zdone_expected += (unsigned long long)nzone;
+                const EvPair e0 = timing_events(h, 0, took);
+                if (took == 2) {
+                    const PairHandover ph{ha, h->d_desc_b, h->d_tile_b, h->d_ring_b};
+                    HIPCHK(h, launch_sweep_pair<T>(fin, fout, sa, ph, rows, h->g.pull, h->stream3, e0.t0, e0.t1,
+                                                   reverse_sweep(h->g, h->steps / 2)));
+                    h->plaunches += 1;
+                } else {
+                    HIPCHK(h, launch_sweep_overlap<T>(fin, fout, sa, ha, h->g.pull, h->stream3, e0.t0, e0.t1,
+                                                      reverse_sweep(h->g, h->steps)));
+                }
+                h->zdone_expected += (unsigned long long)(took * nzone);
                 h->prev_overlapped = true;
+                h->prev_pair = took == 2;
                 joined = false;
             }
         }
         std::swap(h->fA, h->fB);
-        h->steps += 1;
+        h->steps += took;
+        s += took - 1;
     }
     if (!joined) {
         // everything enqueued is ordered before later work on the caller's stream: the sweep
@@ -681,6 +712,20 @@ lbib_status lbib_init(lbib_handle h)
             (e = hipMemcpy(h->d_refs, refs.data(), np * sizeof(PartRef), hipMemcpyHostToDevice)) != hipSuccess)
             return bail(e, "lbib_init: upload");
         h->args_dirty = true;
+    }
+    h->pairs = h->parts.size() <= 1 && pair_sweeps(h->g);
+    if (h->pairs && !h->parts.empty()) {
+        const size_t cap = (size_t)h->parts[0].box_cap, list = align_up(2 * cap * 8), index = align_up((cap + 31) / 32 * 8);
+        e = hipMalloc((void**)&h->d_pair, list + index + sizeof(TileDesc));
+        if (e == hipSuccess) {
+            h->d_tile_b = (int64_t*)h->d_pair;
+            h->d_ring_b = (uint2*)(h->d_pair + list);
+            h->d_desc_b = (TileDesc*)(h->d_pair + list + index);
+        } else {  // no room: one step per sweep
+            (void)hipGetLastError();
+            h->d_pair = nullptr;
+            h->pairs = false;
+        }
     }
     if ((e = hipStreamCreateWithFlags(&h->stream2, hipStreamNonBlocking)) != hipSuccess)
         return bail(e, "lbib_init: second stream");

@@ -20,6 +20,7 @@
 #include "lbib_collide.hpp"
 #include "lbib_device.hpp"
 #include "lbib_internal.hpp"
+#include "lbib_march.hpp"
 
 namespace lbib {
 
@@ -144,7 +145,8 @@ __global__ __launch_bounds__(256, St<T>::neq ? 7 : 8) void sweep_overlap_kernel(
                                                                                  int nblocks, int rev)
 {
     using TL = Tile<PULL>;
-    __shared__ ZoneTiles zs;
+    static_assert(TL::H == 1, "a zone row is a tile row");
+    __shared__ Zone zs;
     __shared__ TileDesc ds;
     const int gx = (int)gxd.d;
     if ((int)blockIdx.x >= c.nzone) {
@@ -155,16 +157,17 @@ __global__ __launch_bounds__(256, St<T>::neq ? 7 : 8) void sweep_overlap_kernel(
         const bool in = i < a.nx && j < a.ny;
         typename St<T>::C g[9];
         if (in) update_load<T, PULL>(fin, a, i, j, g);
-        // each wave learns the box's tiles by itself (no barrier)
-        const ZoneTiles zt = zone_wait_wave(c.zone_words, c.zone_tag, c.flags);
-        if (!in || zone_has_tile(zt, tx, ty, gx)) return;
+        // each wave learns the box by itself (no barrier)
+        const Zone z = zone_wait_wave(c.zone_words, c.zone_tag, c.flags);
+        if (!in || (ty >= z.j0 && ty < z.j0 + z.h && has_col(zone_cols<TL::W>(z, a.nx, gx), tx, gx))) return;
         update_store<T, PULL>(fout, a, i, j, g, a.gx, a.gy);
         return;
     }
     if (threadIdx.x == 0) zs = zone_wait(c.zone_words, c.zone_tag, c.flags);
     __syncthreads();
-    const ZoneTiles zt = zs;
-    const int nt = zt.ntx * zt.nty;
+    const Zone z = zs;
+    const ZoneCols zc = zone_cols<TL::W>(z, a.nx, gx);
+    const int nt = zc.n * z.h;
     const int e0 = (int)blockIdx.x;
     if (e0 < nt) {
         if (threadIdx.x == 0) {
@@ -177,10 +180,10 @@ __global__ __launch_bounds__(256, St<T>::neq ? 7 : 8) void sweep_overlap_kernel(
         // allocation of the whole kernel, whose other workgroups run the plain update
 #pragma unroll 1
         for (int e = e0; e < nt; e += c.nzone) {
-            int tx = zt.tx0 + e % zt.ntx;
+            int tx = zc.c0 + e % zc.n;
             if (tx >= gx) tx -= gx;
-            const int i = tx * TL::W + (int)threadIdx.x % TL::W;
-            const int j = (zt.ty0 + e / zt.ntx) * TL::H + (int)threadIdx.x / TL::W;
+            const int i = tx * TL::W + (int)threadIdx.x;
+            const int j = z.j0 + e / zc.n;
             if (i >= a.nx || j >= a.ny) continue;
             typename St<T>::C g[9];
             update_load<T, PULL>(fin, a, i, j, g);
@@ -193,6 +196,108 @@ __global__ __launch_bounds__(256, St<T>::neq ? 7 : 8) void sweep_overlap_kernel(
     stores_done();
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_fetch_add(c.zdone, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Two steps in one pass (PairHandover).  FP64 keeps three waves per SIMD, the others four.
+// What bounds it: memory (march_pair), and beside a small lattice the particle's chain of two
+// phases, the zone and the units' runs.  Those runs are cut short (two to four rows here,
+// against 16 in the other units): with whole units of 8 rows, and units given by 256-node tiles,
+// 4096 x 1024 took 37.1 us per step (FP32) and 90 (FP64, 960 markers) instead of 35.3 and 75.
+template <typename T, bool PULL>
+__global__ __launch_bounds__(256, sizeof(typename St<T>::raw) == 8 ? 3 : 4) void sweep_pair_kernel(
+    const T* __restrict__ fin, T* __restrict__ fout, SweepArgs a, PairHandover c, FastDiv gud, int nblocks, int rows,
+    int rev)
+{
+    constexpr int U = 4 * kStrip;
+    __shared__ Zone zs;
+    __shared__ TileDesc ds[2];
+    const int gu = (int)gud.d, nzone = c.h.nzone;
+    const int w = wave_row((int)(threadIdx.x >> 6));
+    if ((int)blockIdx.x >= nzone) {
+        int b = xcd_tile((int)blockIdx.x - nzone, nblocks);
+        if (rev) b = nblocks - 1 - b;
+        const int by = (int)fdiv((uint32_t)b, gud), bx = b - by * gu;
+        if (nzone > 0) {
+            const Zone z = zone_wait_wave(c.h.zone_words, c.h.zone_tag, c.h.flags);
+            if (by * rows < z.j0 + z.h && (by + 1) * rows > z.j0 && has_col(zone_cols<U>(z, a.nx, gu), bx, gu)) return;
+        }
+        const int c0 = (4 * bx + w) * kStrip, r0 = by * rows;
+        if (c0 >= a.nx) return;
+        march_pair<T, PULL>(fin, fout, a, c0, r0, min(r0 + rows, a.ny), BoxForce{}, BoxForce{});
+        return;
+    }
+    if (threadIdx.x == 0) {
+        zs = zone_wait(c.h.zone_words, c.h.zone_tag, c.h.flags);
+        wait_counter(c.h.ready, c.h.ready_target, c.h.flags);
+        ds[0] = coherent_load(c.h.desc);
+    }
+    __syncthreads();
+    // the units the zone reaches, in runs short enough that the workgroups take one each where
+    // they can: a run's rows go one after the other, and the particle's next step waits for them
+    const Zone z = zs;
+    const ZoneCols uc = zone_cols<U>(z, a.nx, gu);
+    const int ub = z.j0 / rows * rows, ue = z.h > 0 ? min(((z.j0 + z.h - 1) / rows + 1) * rows, a.ny) : ub;
+    const int run = max((ue - ub) * uc.n / nzone + 1, 2), nrun = (ue - ub + run - 1) / run;
+    const int nu = uc.n * nrun;
+    BoxForce f1{ds[0], c.h.tile, c.h.ring};
+    // step n at the nodes of the widened box, if its units are here to overwrite them
+    if (f1.d.active && nu > 0) {
+        const TileDesc d = f1.d;
+        const Zone zn = widened(d, a.nx, a.ny, kZoneMargin);
+        const int per = (zn.w + 63) / 64, lane = (int)(threadIdx.x & 63);
+#pragma unroll 1
+        for (int e = (int)blockIdx.x * 4 + w; e < zn.h * per; e += 4 * nzone) {
+            const int j = zn.j0 + e / per, cc = (e % per) * 64 + lane;
+            if (cc >= zn.w) continue;
+            int i = zn.i0 + cc;
+            if (i >= a.nx) i -= a.nx;
+            typename St<T>::C g[9];
+            update_load<T, PULL>(fin, a, i, j, g);
+            double Fx = a.gx, Fy = a.gy;
+            box_force<true>(d, f1.tile, f1.ring, i, j, a.nx, Fx, Fy);
+            update_store<T, PULL, true>(fout, a, i, j, g, Fx, Fy);
+        }
+    }
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __hip_atomic_fetch_add(c.h.zdone, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_counter(c.h.ready, c.h.ready_target + 1, c.h.flags);
+        ds[1] = coherent_load(c.desc_b);
+    }
+    __syncthreads();
+    const BoxForce f2{ds[1], c.tile_b, c.ring_b};
+#pragma unroll 1
+    for (int e = (int)blockIdx.x; e < nu; e += nzone) {
+        int bx = uc.c0 + e % uc.n;
+        if (bx >= gu) bx -= gu;
+        const int r0 = ub + e / uc.n * run;
+        // a wave whose strip lies past the lattice's end runs along (it stores nothing)
+        march_pair<T, PULL, true>(fin, fout, a, min((4 * bx + w) * kStrip, a.nx), r0, min(r0 + run, ue), f1, f2);
+    }
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_fetch_add(c.h.zdone, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <typename T>
+hipError_t launch_sweep_pair(const T* fin, T* fout, const SweepArgs& a, const PairHandover& c, int32_t rows, bool pull,
+                             hipStream_t stream, hipEvent_t t0, hipEvent_t t1, bool rev)
+{
+    if (c.h.nzone < 0 || c.h.nzone > 64 || c.h.nzone % 8 || rows < 1) return hipErrorInvalidValue;
+    if constexpr (St<T>::neq) {
+        return hipErrorInvalidValue;
+    } else {
+        const int gu = (a.nx + 4 * kStrip - 1) / (4 * kStrip), nb = gu * ((a.ny + rows - 1) / rows);
+        const dim3 grid(nb + c.h.nzone);
+        if (pull)
+            hipExtLaunchKernelGGL(sweep_pair_kernel<T, true>, grid, dim3(256), 0u, stream, t0, t1, 0u, fin, fout, a, c,
+                                  make_fastdiv(gu), nb, (int)rows, (int)rev);
+        else
+            hipExtLaunchKernelGGL(sweep_pair_kernel<T, false>, grid, dim3(256), 0u, stream, t0, t1, 0u, fin, fout, a, c,
+                                  make_fastdiv(gu), nb, (int)rows, (int)rev);
+        return hipGetLastError();
+    }
 }
 
 // Sweep of a step with several particles (64 x 4 tiles, a row per wave: those of the tile mask).
@@ -276,6 +381,8 @@ hipError_t launch_sweep_overlap(const T* fin, T* fout, const SweepArgs& a, const
                                         const uint2*, bool, hipStream_t, hipEvent_t, hipEvent_t, bool);                               \
     template hipError_t launch_sweep_overlap<T>(const T*, T*, const SweepArgs&, const HandoverArgs&, bool,         \
                                                 hipStream_t, hipEvent_t, hipEvent_t, bool);                       \
+    template hipError_t launch_sweep_pair<T>(const T*, T*, const SweepArgs&, const PairHandover&, int32_t, bool,   \
+                                             hipStream_t, hipEvent_t, hipEvent_t, bool);                          \
     template hipError_t launch_sweep_multi<T>(const T*, T*, const SweepArgs&, const unsigned long long*,           \
                                               unsigned long long*, const PartRef*, bool, hipStream_t, hipEvent_t,  \
                                               hipEvent_t);
