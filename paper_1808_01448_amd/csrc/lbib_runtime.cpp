@@ -298,6 +298,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
     if (split && h->args_dirty) {
         lbib_status st = upload_split_args<T>(h);
         if (st != LBIB_OK) return st;
+        idle = false;  // the second stream's launches read the arguments this copy brings
     }
     for (int64_t s = 0; s < n; ++s) {
         const T* fin = (const T*)h->fA;
