@@ -250,7 +250,9 @@ lbib_status lbib_load(lbib_handle h, const void* blob, int64_t size);
  * per step, and such a launch can be dispatched only once a running sweep drains, which may
  * leave it a sweep behind for the rest of the call.  On lattices whose sweep moves 16 MB or more
  * per step (and always there without particles) mode 2 sweeps two steps in one pass over memory,
- * a call's last odd step alone; the f - f_eq storages keep one step per sweep.  All schedules
+ * a call's last odd step alone; the f - f_eq storages keep one step per sweep.  A call too short
+ * to win back the hand-over between its streams (one step of any lattice, up to six of a small
+ * one) runs serially in mode 2.  All schedules
  * give bit-identical results. */
 /* Several particles in one lattice: the particle phase is split in two halves over all
  * particles -- first every particle stages its box and spreads its marker forces, then every

@@ -342,6 +342,18 @@ struct ParticleRun {
 template <typename T>
 hipError_t launch_particle_run(const ParticleArgs<T>& a, const ParticleRun<T>& run, hipStream_t stream,
                                hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// What a step call leaves in pinned host memory at its end, so that the reads after it need no
+// copy from the device: the flags word at out[0], and for each of n particles, from out + off,
+// the record of its last step and its nl bond flags.
+struct ReportItem {
+    const DevParticle* st;
+    const uint8_t* bond;
+    int32_t nl;
+    uint32_t off;
+};
+constexpr uint32_t kReportHead = 16;  // bytes of out before the first particle's
+hipError_t launch_report(const ReportItem* items, int32_t n, const int32_t* flags, unsigned char* out,
+                         hipStream_t stream);
 // The two launches of the split particle phase (mode 1: spread and mark; mode 2: loads,
 // bonds, update), one workgroup per particle of args[0..n); lds: the dynamic LDS of the
 // launch (the most particle_launch_lds of the particles).  ch: the device-side hand-over when

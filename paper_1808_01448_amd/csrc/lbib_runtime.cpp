@@ -64,11 +64,15 @@ struct lbib_sim {
     void* fB = nullptr;
     std::vector<Particle> parts;
     int32_t* d_flags = nullptr;
-    // the flags word as of the end of the last lbib_step call, copied (stream-ordered) into
-    // pinned host memory at that call's end, and the event that marks that end: lbib_sync and
-    // the reads take the flags from there instead of a synchronous copy after their wait
-    int32_t* h_flags = nullptr;
-    bool h_flags_valid = false;
+    // the flags word, the particles' records and their bond flags as of the end of the last
+    // lbib_step call (ReportItem), written (stream-ordered) into pinned host memory at that
+    // call's end, and the event that marks that end: lbib_sync and the reads take them from
+    // there instead of a synchronous copy after their wait.  report_valid: the records and bonds
+    // too (no write of the state since)
+    unsigned char* h_report = nullptr;
+    std::vector<uint32_t> report_off;
+    ReportItem* d_items = nullptr;
+    bool h_flags_valid = false, report_valid = false;
     hipEvent_t ev_end = nullptr;
     int64_t steps = 0;
     FieldStage stage;
@@ -154,9 +158,10 @@ void free_all(lbib_sim* h)
     if (h->fB) (void)hipFree(h->fB);
     h->fA = h->fB = nullptr;
     dfree(h->d_flags);
-    if (h->h_flags) (void)hipHostFree(h->h_flags);
-    h->h_flags = nullptr;
-    h->h_flags_valid = false;
+    if (h->h_report) (void)hipHostFree(h->h_report);
+    h->h_report = nullptr;
+    h->h_flags_valid = h->report_valid = false;
+    dfree(h->d_items);
     if (h->ev_end) (void)hipEventDestroy(h->ev_end);
     h->ev_end = nullptr;
     dfree(h->stage.p);
@@ -274,6 +279,16 @@ hipError_t ensure_sweep_stream(lbib_sim* h)
     return hipStreamCreateWithFlags(&h->stream3, hipStreamNonBlocking);
 }
 
+// Mode 2 runs a call too short to win its streams' hand-over back serially: each overlapped step
+// hides the shorter of the sweep and the particle phase (about 16 us), the call's join of the
+// two chains costs about 24 us (a step and a wait on 256 x 64 FP64: 34 us serially, 55 us
+// overlapped).
+bool short_call(const LatticeGeom& g, int64_t n)
+{
+    const double sweep_us = 3.0 + (double)g.upd_bytes * g.nx * g.ny / 6e6;
+    return (double)n * std::min(sweep_us, 16.0) < 24.0;
+}
+
 // One time step is the particle phase then the lattice sweep; mode 2 of a large lattice, and a
 // lattice without particles, sweep two steps in one pass over memory (PairHandover).  Serial schedule: both on the
 // caller's stream.  Overlapped schedule (when the previous step has predicted this step's
@@ -293,7 +308,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
     // call enqueues on it clears this
     bool idle = stream_idle(h->stream);
     int64_t run_left = 0;  // steps still covered by the resident particle launch already enqueued
-    h->h_flags_valid = false;  // until this call's copy is enqueued
+    h->h_flags_valid = h->report_valid = false;  // until this call's report is enqueued
     const bool split = h->parts.size() > 1 || (h->overlap == 3 && !h->parts.empty());
     if (split && h->args_dirty) {
         lbib_status st = upload_split_args<T>(h);
@@ -397,7 +412,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
             // 8192 x 4096 (the particle phase hides behind the sweep).  It needs the CU-masked
             // sweep stream: workgroups of the sweep and the particle's wait for each other on
             // the device, and the particle must always find a CU.
-            bool overlap = h->overlap == 1 || h->overlap == 2;
+            bool overlap = h->overlap == 1 || (h->overlap == 2 && !short_call(h->g, n));
             if (h->desc.ny >= (1 << 23)) overlap = false;  // the packed tiles (zone_pack)
             if (overlap && h->zone_valid) HIPCHK(h, ensure_sweep_stream(h));
             if (!h->masked) overlap = false;
@@ -487,9 +502,9 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
         HIPCHK(h, hipStreamWaitEvent(h->stream, h->evB, 0));
     }
     if (n > 0) {
-        HIPCHK(h, hipMemcpyAsync(h->h_flags, h->d_flags, sizeof(int32_t), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(h, launch_report(h->d_items, (int32_t)h->parts.size(), h->d_flags, h->h_report, h->stream));
         HIPCHK(h, hipEventRecord(h->ev_end, h->stream));
-        h->h_flags_valid = true;
+        h->h_flags_valid = h->report_valid = true;
     }
     return LBIB_OK;
 }
@@ -500,7 +515,7 @@ lbib_status check_flags(lbib_sim* h)
 {
     int32_t fl = 0;
     if (h->h_flags_valid)
-        fl = *(volatile int32_t*)h->h_flags;
+        fl = *(volatile int32_t*)h->h_report;
     else
         HIPCHK(h, hipMemcpy(&fl, h->d_flags, sizeof(fl), hipMemcpyDeviceToHost));
     if (fl) {
@@ -519,7 +534,7 @@ lbib_status check_flags(lbib_sim* h)
 // Waits for the handle's stream.  The end of the last lbib_step call is polled for up to
 // 2 ms first (a blocking wait's wake-up costs tens of microseconds, a large share of a short
 // call); longer waits block.
-lbib_status sync_check(lbib_sim* h)
+lbib_status wait_stream(lbib_sim* h)
 {
     if (h->h_flags_valid) {
         const auto t0 = std::chrono::steady_clock::now();
@@ -529,7 +544,13 @@ lbib_status sync_check(lbib_sim* h)
         if (q != hipSuccess && q != hipErrorNotReady) return hip_fail(h, q, "hipEventQuery");
     }
     if (!stream_idle(h->stream)) HIPCHK(h, hipStreamSynchronize(h->stream));
-    return check_flags(h);
+    return LBIB_OK;
+}
+
+lbib_status sync_check(lbib_sim* h)
+{
+    const lbib_status s = wait_stream(h);
+    return s == LBIB_OK ? check_flags(h) : s;
 }
 
 Particle* get_particle(lbib_sim* h, int32_t pid)
@@ -676,11 +697,22 @@ lbib_status lbib_init(lbib_handle h)
     };
     if ((e = hipMemsetAsync(h->fB, 0, bytes, h->stream)) != hipSuccess) return bail(e, "hipMemset");
     if ((e = hipMemsetAsync(h->d_flags, 0, sizeof(int32_t), h->stream)) != hipSuccess) return bail(e, "hipMemset");
-    if ((e = hipHostMalloc((void**)&h->h_flags, sizeof(int32_t), hipHostMallocDefault)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&h->ev_end, hipEventDisableTiming)) != hipSuccess)
-        return bail(e, "lbib_init: pinned flags");
-    *h->h_flags = 0;
-    h->h_flags_valid = false;
+    size_t report = kReportHead;
+    std::vector<ReportItem> items;
+    h->report_off.clear();
+    for (auto& p : h->parts) {
+        items.push_back(ReportItem{p.d_st, p.d_bond, p.nl, (uint32_t)report});
+        h->report_off.push_back((uint32_t)report);
+        report += (sizeof(lbib_particle_state) + p.nl + 15) / 16 * 16;
+    }
+    if ((e = hipHostMalloc((void**)&h->h_report, report, hipHostMallocDefault)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&h->ev_end, hipEventDisableTiming)) != hipSuccess ||
+        (e = dalloc(&h->d_items, items.size())) != hipSuccess ||
+        (!items.empty() && (e = hipMemcpy(h->d_items, items.data(), items.size() * sizeof(ReportItem),
+                                          hipMemcpyHostToDevice)) != hipSuccess))
+        return bail(e, "lbib_init: report of the steps");
+    std::memset(h->h_report, 0, report);
+    h->h_flags_valid = h->report_valid = false;
     if ((e = init_populations(h->fA, h->g, h->stream)) != hipSuccess) return bail(e, "init kernel");
     if ((e = hipStreamSynchronize(h->stream)) != hipSuccess) return bail(e, "lbib_init: sync");
     for (auto& p : h->parts)
@@ -777,10 +809,15 @@ lbib_status lbib_read_particle(lbib_handle h, int32_t pid, lbib_particle_state* 
     Particle* p = get_particle(h, pid);
     if (!p) return fail(h, LBIB_E_INVALID, "lbib_read_particle: unknown particle id");
     if (h->state == 0) return fail(h, LBIB_E_STATE, "lbib_read_particle: lbib_init first");
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    DevParticle st;
-    HIPCHK(h, hipMemcpy(&st, p->d_st, sizeof(st), hipMemcpyDeviceToHost));
-    *out = st.last;
+    const lbib_status w = wait_stream(h);
+    if (w != LBIB_OK) return w;
+    if (h->report_valid) {
+        std::memcpy(out, h->h_report + h->report_off[pid], sizeof(*out));
+    } else {
+        DevParticle st;
+        HIPCHK(h, hipMemcpy(&st, p->d_st, sizeof(st), hipMemcpyDeviceToHost));
+        *out = st.last;
+    }
     return check_flags(h);
 }
 
@@ -791,8 +828,12 @@ lbib_status lbib_read_bonds(lbib_handle h, int32_t pid, uint8_t* bonded, uint8_t
     if (!p) return fail(h, LBIB_E_INVALID, "lbib_read_bonds: unknown particle id");
     if (h->state == 0) return fail(h, LBIB_E_STATE, "lbib_read_bonds: lbib_init first");
     if (capacity < p->nl) return fail(h, LBIB_E_INVALID, "lbib_read_bonds: capacity must be >= " + std::to_string(p->nl));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    if (bonded) HIPCHK(h, hipMemcpy(bonded, p->d_bond, p->nl, hipMemcpyDeviceToHost));
+    const lbib_status w = wait_stream(h);
+    if (w != LBIB_OK) return w;
+    if (bonded && h->report_valid)
+        std::memcpy(bonded, h->h_report + h->report_off[pid] + sizeof(lbib_particle_state), p->nl);
+    else if (bonded)
+        HIPCHK(h, hipMemcpy(bonded, p->d_bond, p->nl, hipMemcpyDeviceToHost));
     if (ligand) std::memcpy(ligand, p->ligand.data(), p->nl);
     return check_flags(h);
 }
@@ -881,6 +922,7 @@ lbib_status lbib_write_particle(lbib_handle h, int32_t pid, const double* v)
     st.om1 = v[11];
     HIPCHK(h, hipMemcpy(p->d_st, &st, sizeof(st), hipMemcpyHostToDevice));
     h->zone_valid = false;  // the predicted box no longer matches the particle
+    h->report_valid = false;
     return LBIB_OK;
 }
 
@@ -896,6 +938,7 @@ lbib_status lbib_write_bonds(lbib_handle h, int32_t pid, const uint8_t* bonded, 
             return fail(h, LBIB_E_INVALID, "lbib_write_bonds: flags must be 0/1 and only on ligand elements");
     HIPCHK(h, hipStreamSynchronize(h->stream));
     HIPCHK(h, hipMemcpy(p->d_bond, bonded, p->nl, hipMemcpyHostToDevice));
+    h->report_valid = false;
     return LBIB_OK;
 }
 
@@ -999,7 +1042,7 @@ lbib_status lbib_load(lbib_handle h, const void* blob, int64_t size)
     }
     const int32_t zero = 0;
     HIPCHK(h, hipMemcpy(h->d_flags, &zero, sizeof(zero), hipMemcpyHostToDevice));
-    h->h_flags_valid = false;
+    h->h_flags_valid = h->report_valid = false;
     h->steps = hd.steps;
     h->state = 1;
     h->zone_valid = false;
