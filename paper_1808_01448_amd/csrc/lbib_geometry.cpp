@@ -8,6 +8,7 @@
 // geometrically; the trapezoid rule gives them to round-off, and integrating the series
 // term by term gives s(t) in closed form.  Newton's method then places each vertex.
 #include <cmath>
+#include <mutex>
 #include <vector>
 
 #include "lbib_geometry.hpp"
@@ -34,12 +35,34 @@ struct ArcSeries {
     }
 };
 
+constexpr int N = 4096;  // samples over one period [0, pi)
+
+// Row m of the cosine transform, cos(2 m theta_k) at the N samples: the same for every ellipse,
+// so each row is computed once in the process, when a series first reaches it (kRows of them at
+// most are kept, 2 MB; a series goes beyond that only for aspect ratios above about 5).  The
+// transform of one ellipse took 1.7-2.6 ms of cosines, most of the time of preparing a particle.
+constexpr int kRows = 64;
+const double* cos_row(int m, std::vector<double>& own)
+{
+    static std::once_flag once[kRows];
+    static std::vector<double> rows[kRows];
+    auto fill = [m](std::vector<double>& r) {
+        r.resize(N);
+        for (int k = 0; k < N; ++k) r[k] = std::cos(2.0 * m * M_PI * k / N);
+    };
+    if (m >= kRows) {
+        fill(own);
+        return own.data();
+    }
+    std::call_once(once[m], [&] { fill(rows[m]); });
+    return rows[m].data();
+}
+
 ArcSeries make_series(double a, double b)
 {
     ArcSeries S;
     S.a = a;
     S.b = b;
-    const int N = 4096;  // samples over one period [0, pi)
     std::vector<double> v(N);
     for (int k = 0; k < N; ++k) v[k] = S.speed(M_PI * k / N);
     double s0 = 0.0;
@@ -48,9 +71,11 @@ ArcSeries make_series(double a, double b)
     const double scale = std::fabs(S.c0);
     // the coefficients fall geometrically, as ((a - b) / (a + b))^m; below ~1e-14 of the mean
     // they are the trapezoid sums' round-off, so the series stops there
+    std::vector<double> own;
     for (int m = 1; m < N / 2; ++m) {
         double cm = 0.0;
-        for (int k = 0; k < N; ++k) cm += v[k] * std::cos(2.0 * m * M_PI * k / N);
+        const double* c = cos_row(m, own);
+        for (int k = 0; k < N; ++k) cm += v[k] * c[k];
         cm *= 2.0 / N;
         if (m > 8 && std::fabs(cm) < 1e-14 * scale) break;
         S.c.push_back(cm);

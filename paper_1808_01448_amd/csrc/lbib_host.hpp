@@ -111,6 +111,13 @@ lbib_status prepare_particle(const lbib_lattice_desc& lat, const lbib_particle_d
 void set_ligands(Particle& p, const lbib_ligand_desc& d);
 LatticeGeom lattice_geom(const lbib_lattice_desc& d);
 
+// A pool's lbib_pool_footprint and lbib_pool_add in two parts, for a caller that keeps the
+// prepared particle (its surface is most of the work) from the first to the second.
+lbib_status pool_prepare(const lbib_lattice_desc& lat, const lbib_particle_desc& pd, Particle& p, int64_t& bytes,
+                         std::string& msg);
+lbib_status pool_add_prepared(lbib_pool* h, const lbib_lattice_desc& lat, const Particle& p,
+                              const lbib_ligand_desc& lig, int64_t n_steps, int32_t* slot);
+
 // Device bytes a simulation of this lattice and particle (or none) needs.
 int64_t footprint_bytes(const lbib_lattice_desc& lat, const Particle* p);
 

@@ -470,6 +470,68 @@ std::string flag_text(int32_t fl)
 
 }  // namespace
 
+lbib_status lbib::pool_prepare(const lbib_lattice_desc& lat, const lbib_particle_desc& pd, Particle& p, int64_t& bytes,
+                               std::string& msg)
+{
+    lbib_status s = check_lattice(lat, msg);
+    if (s == LBIB_OK) s = prepare_particle(lat, pd, p, msg);
+    if (s == LBIB_OK) bytes = footprint_bytes(lat, &p);
+    return s;
+}
+
+// The particle is prepared for this lattice, whose precision is the pool's.
+lbib_status lbib::pool_add_prepared(lbib_pool* h, const lbib_lattice_desc& lat, const Particle& p,
+                                    const lbib_ligand_desc& lig, int64_t n_steps, int32_t* slot)
+{
+    std::unique_ptr<Member> m;
+    try {
+        m.reset(new Member());
+        m->p = p;
+        set_ligands(m->p, lig);
+    } catch (const std::bad_alloc&) {
+        return fail(h, LBIB_E_NOMEM, "lbib_pool_add: host allocation failed");
+    }
+    m->lat = lat;
+    m->g = lattice_geom(lat);
+    m->g.pull = true;  // the pool sweep runs the pull update
+    m->target = n_steps;
+    m->bytes = footprint_bytes(lat, &m->p);
+    if (h->free_lanes.empty()) return fail(h, LBIB_E_FULL, "lbib_pool_add: max_members members already in the pool");
+    if (h->in_use + m->bytes > h->budget)
+        return fail(h, LBIB_E_FULL,
+                    "lbib_pool_add: needs " + std::to_string(m->bytes) + " bytes, " +
+                        std::to_string(h->budget - h->in_use) + " left in the budget");
+    m->block = h->arena.alloc((size_t)m->bytes);
+    if (!m->block) return fail(h, LBIB_E_FULL, "lbib_pool_add: no contiguous free block of the budget is large enough");
+    const size_t pop = align_up(m->g.buf_bytes);
+    m->fA = m->block;
+    m->fB = m->block + pop;
+    carve_particle(m->p, m->block + 2 * pop);
+    m->lane = h->free_lanes.back();
+    m->p.d_st = h->d_st + m->lane;  // the pool-wide lane replaces the block's own state slot
+    // everything below is stream-ordered: the member's first step sees it complete
+    hipError_t e;
+    auto bail = [&](hipError_t err, const char* what) {
+        (void)hipStreamSynchronize(h->stream);
+        free_member(h, *m);
+        return hip_fail(h, err, what);
+    };
+    if ((e = hipMemsetAsync(m->fB, 0, pop, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: hipMemset");
+    if ((e = hipMemsetAsync(h->d_flags + m->lane, 0, sizeof(int32_t), h->stream)) != hipSuccess)
+        return bail(e, "lbib_pool_add: hipMemset");
+    if ((e = init_populations(m->fA, m->g, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: init kernel");
+    if ((e = upload_particle(m->p, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: upload");
+    h->cache_valid = false;
+    h->free_lanes.pop_back();
+    m->slot = h->next_slot++;
+    m->state = n_steps > 0 ? LBIB_POOL_RUNNING : LBIB_POOL_FINISHED;
+    h->in_use += m->bytes;
+    *slot = m->slot;
+    h->members[m->slot] = std::move(m);
+    h->dirty = true;
+    return LBIB_OK;
+}
+
 extern "C" {
 
 lbib_status lbib_pool_create(int32_t precision, int64_t hbm_budget_bytes, int32_t max_members, void* hip_stream,
@@ -529,13 +591,10 @@ lbib_status lbib_pool_footprint(const lbib_lattice_desc* lat, const lbib_particl
 {
     if (!lat || !pd || !bytes) return fail(nullptr, LBIB_E_INVALID, "lbib_pool_footprint: NULL argument");
     std::string msg;
-    lbib_status s = check_lattice(*lat, msg);
-    if (s != LBIB_OK) return fail(nullptr, s, "lbib_pool_footprint: " + msg);
     try {
         Particle p;
-        s = prepare_particle(*lat, *pd, p, msg);
+        const lbib_status s = pool_prepare(*lat, *pd, p, *bytes, msg);
         if (s != LBIB_OK) return fail(nullptr, s, "lbib_pool_footprint: " + msg);
-        *bytes = footprint_bytes(*lat, &p);
     } catch (const std::bad_alloc&) {
         return fail(nullptr, LBIB_E_NOMEM, "lbib_pool_footprint: host allocation failed");
     }
@@ -554,53 +613,13 @@ lbib_status lbib_pool_add(lbib_pool_handle h, const lbib_lattice_desc* lat, cons
     if (lat->precision != h->precision)
         return fail(h, LBIB_E_INVALID, "lbib_pool_add: lattice precision differs from the pool's");
     if ((s = check_ligands(*lig, msg)) != LBIB_OK) return fail(h, s, "lbib_pool_add: " + msg);
-    std::unique_ptr<Member> m;
     try {
-        m.reset(new Member());
-        if ((s = prepare_particle(*lat, *pd, m->p, msg)) != LBIB_OK) return fail(h, s, "lbib_pool_add: " + msg);
-        set_ligands(m->p, *lig);
+        Particle p;
+        if ((s = prepare_particle(*lat, *pd, p, msg)) != LBIB_OK) return fail(h, s, "lbib_pool_add: " + msg);
+        return pool_add_prepared(h, *lat, p, *lig, n_steps, slot);
     } catch (const std::bad_alloc&) {
         return fail(h, LBIB_E_NOMEM, "lbib_pool_add: host allocation failed");
     }
-    m->lat = *lat;
-    m->g = lattice_geom(*lat);
-    m->g.pull = true;  // the pool sweep runs the pull update
-    m->target = n_steps;
-    m->bytes = footprint_bytes(*lat, &m->p);
-    if (h->free_lanes.empty()) return fail(h, LBIB_E_FULL, "lbib_pool_add: max_members members already in the pool");
-    if (h->in_use + m->bytes > h->budget)
-        return fail(h, LBIB_E_FULL,
-                    "lbib_pool_add: needs " + std::to_string(m->bytes) + " bytes, " +
-                        std::to_string(h->budget - h->in_use) + " left in the budget");
-    m->block = h->arena.alloc((size_t)m->bytes);
-    if (!m->block) return fail(h, LBIB_E_FULL, "lbib_pool_add: no contiguous free block of the budget is large enough");
-    const size_t pop = align_up(m->g.buf_bytes);
-    m->fA = m->block;
-    m->fB = m->block + pop;
-    carve_particle(m->p, m->block + 2 * pop);
-    m->lane = h->free_lanes.back();
-    m->p.d_st = h->d_st + m->lane;  // the pool-wide lane replaces the block's own state slot
-    // everything below is stream-ordered: the member's first step sees it complete
-    hipError_t e;
-    auto bail = [&](hipError_t err, const char* what) {
-        (void)hipStreamSynchronize(h->stream);
-        free_member(h, *m);
-        return hip_fail(h, err, what);
-    };
-    if ((e = hipMemsetAsync(m->fB, 0, pop, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: hipMemset");
-    if ((e = hipMemsetAsync(h->d_flags + m->lane, 0, sizeof(int32_t), h->stream)) != hipSuccess)
-        return bail(e, "lbib_pool_add: hipMemset");
-    if ((e = init_populations(m->fA, m->g, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: init kernel");
-    if ((e = upload_particle(m->p, h->stream)) != hipSuccess) return bail(e, "lbib_pool_add: upload");
-    h->cache_valid = false;
-    h->free_lanes.pop_back();
-    m->slot = h->next_slot++;
-    m->state = n_steps > 0 ? LBIB_POOL_RUNNING : LBIB_POOL_FINISHED;
-    h->in_use += m->bytes;
-    *slot = m->slot;
-    h->members[m->slot] = std::move(m);
-    h->dirty = true;
-    return LBIB_OK;
 }
 
 lbib_status lbib_pool_step(lbib_pool_handle h, int64_t n)

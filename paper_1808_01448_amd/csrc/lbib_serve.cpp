@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "lbib.h"
+#include "lbib_host.hpp"
 
 namespace {
 
@@ -21,6 +22,7 @@ struct Request {
     lbib_lattice_desc lat{};
     lbib_particle_desc part{};
     lbib_ligand_desc lig{};
+    lbib::Particle prepared;  // from the submission, for the admission
     int64_t steps = 0;
     int64_t bytes = 0;
     int32_t bypassed = 0;  // admissions of later requests while this one waited at the head
@@ -41,6 +43,7 @@ double now_s(std::chrono::steady_clock::time_point t0)
 
 struct lbib_server {
     lbib_pool_handle pool = nullptr;
+    int32_t precision = 0;
     int32_t chunk = 0;
     int32_t max_bypass = 0;
     int64_t budget = 0;
@@ -73,6 +76,18 @@ lbib_status pool_fail(lbib_server* h, lbib_status s, const char* what)
     return fail(h, s, std::string(what) + ": " + lbib_pool_last_error(h->pool));
 }
 
+// lbib_pool_add of a request, whose lattice and particle were validated and prepared when it was
+// submitted.
+lbib_status add_to_pool(lbib_server* h, Request& r, int32_t* slot)
+{
+    std::string msg;
+    if (r.lat.precision != h->precision) return LBIB_E_INVALID;
+    lbib_status s = lbib::check_ligands(r.lig, msg);
+    if (s == LBIB_OK) s = lbib::pool_add_prepared(h->pool, r.lat, r.prepared, r.lig, r.steps, slot);
+    if (s == LBIB_OK) r.prepared = lbib::Particle{};
+    return s;
+}
+
 // Admit waiting requests, first fit in arrival order: a request that does not fit the free
 // memory is passed over by later ones that do, but at most max_bypass times; then nothing
 // behind it is admitted until it is.
@@ -91,7 +106,7 @@ lbib_status admit(lbib_server* h)
             continue;
         }
         int32_t slot = -1;
-        s = lbib_pool_add(h->pool, &r->lat, &r->part, &r->lig, r->steps, &slot);
+        s = add_to_pool(h, *r, &slot);
         if (s == LBIB_E_FULL) break;  // out of slots: nothing else can join now
         if (s != LBIB_OK) {
             // a request the pool refuses (its descriptors were checked at submission, so this
@@ -197,6 +212,7 @@ lbib_status lbib_server_create(int32_t precision, int64_t hbm_budget_bytes, int3
         delete h;
         return fail(nullptr, s, m);
     }
+    h->precision = precision;
     h->chunk = chunk_steps;
     h->max_bypass = max_bypass;
     h->budget = hbm_budget_bytes;
@@ -211,14 +227,17 @@ lbib_status lbib_server_submit(lbib_server_handle h, const lbib_lattice_desc* la
     if (!h) return fail(nullptr, LBIB_E_INVALID, "lbib_server_submit: NULL handle");
     if (!lat || !part || !lig || !id) return fail(h, LBIB_E_INVALID, "lbib_server_submit: NULL argument");
     if (n_steps < 0) return fail(h, LBIB_E_INVALID, "lbib_server_submit: negative step count");
-    int64_t bytes = 0;
-    lbib_status s = lbib_pool_footprint(lat, part, &bytes);
-    if (s != LBIB_OK) return fail(h, s, std::string("lbib_server_submit: ") + lbib_pool_last_error(nullptr));
-    if (bytes > h->budget)
-        return fail(h, LBIB_E_FULL, "lbib_server_submit: the request alone exceeds the memory budget");
     Request* r = nullptr;
     try {
+        lbib::Particle p;
+        int64_t bytes = 0;
+        std::string msg;
+        const lbib_status s = lbib::pool_prepare(*lat, *part, p, bytes, msg);
+        if (s != LBIB_OK) return fail(h, s, "lbib_server_submit: lbib_pool_footprint: " + msg);
+        if (bytes > h->budget)
+            return fail(h, LBIB_E_FULL, "lbib_server_submit: the request alone exceeds the memory budget");
         r = new Request();
+        r->prepared = std::move(p);
         r->id = h->next_id;
         r->lat = *lat;
         r->part = *part;
