@@ -225,6 +225,7 @@ struct ParticleArgs {
     unsigned long long zdone_target;
     int32_t check_prev;
     int32_t pair_first;
+    int32_t no_predict;  // nothing reads the prediction of the next step's box
     // the one-launch split phase: grid-barrier counter and the value this launch waits for
     unsigned long long* bar;
     unsigned long long bar_target;
@@ -414,7 +415,7 @@ struct PoolSweepConfig {
 };
 // lds: the dynamic LDS of the launch (the most particle_launch_lds of the members).
 constexpr int kPairStrip = 62;  // result columns of a wave of the two-step sweeps (lbib_march.hpp)
-// half: 0 the step (or the first of two), 1 the second of two.
+// half: 0 the first of two steps swept together, 1 the second, 2 a step swept alone.
 template <typename T>
 hipError_t launch_pool_particle(const ParticleArgs<T>* args, const PoolSweep<T>* sims, const int32_t* active,
                                 TileDesc* ctl, int32_t n_active, int32_t half, int32_t max_nl, size_t lds,

@@ -271,6 +271,21 @@ __device__ __forceinline__ void set_bounds(const MarkerSet<MPT>& G, int ny, int*
     }
 }
 
+// The workgroup's totals of set_bounds in r[0..3] and, in r[4], the ligands within y_cr of the
+// wall.
+template <int MPT, typename T>
+__device__ __forceinline__ void box_bounds(const MarkerSet<MPT>& G, const MarkerData<MPT>& D, const ParticleArgs<T>& a,
+                                           int (*shi)[NW], int (&r)[5])
+{
+    r[0] = r[1] = r[2] = r[3] = 0x7fffffff;
+    r[4] = 0;
+    set_bounds<MPT>(G, a.ny, r);
+#pragma unroll
+    for (int k = 0; k < MPT; ++k) r[4] += D.lig[k] && G.Y[k] + 0.5 < a.y_cr ? 1 : 0;
+    const int op[5] = {2, 2, 2, 2, 0};
+    block_int<5>(r, op, shi);
+}
+
 // Set the mask bits of the support window at (X, Y) (the full window of mls_shape: nodes of
 // zero weight are read too, multiplied by zero); a window row is at most 3 nodes, so one
 // atomic per mask word it touches.
@@ -710,6 +725,16 @@ __device__ __forceinline__ void mark_tiles(const ParticleArgs<T>& a, int x0, int
 // A double of the particle state, stored coherently across the XCDs' L2 caches.
 __device__ __forceinline__ void state_store(double* p, double v) { coherent_store((int64_t*)p, __double_as_longlong(v)); }
 
+// What a step of a resident particle launch leaves in LDS for the next one: the state it starts
+// from and, from the prediction of its box, the pose's cosine and sine, the box bounds and the
+// probing ligands (set_bounds), which the next step would otherwise read and form again.
+struct PhaseCarry {
+    double xc, yc, th, ux, uy, om, xc1, yc1, th1, ux1, uy1, om1, cth, sth;
+    int64_t step;
+    int32_t r[5];
+    int32_t valid;
+};
+
 // What the first part of the particle phase hands to the rest.
 template <int MPT>
 struct PhaseCtx {
@@ -717,13 +742,14 @@ struct PhaseCtx {
     double xc1, yc1, th1, ux1, uy1, om1;  // level n-1
     int64_t step;
     int x0, y0, w, h, nbox, nmarked, nprobe, flags;
-    bool box_ok;
+    bool box_ok, whole;
     const uint32_t* mask;
     const int* pre;
     const int* nodes;
     MarkerSet<MPT> G;
     MarkerData<MPT> D;
     TileDesc zin;
+    PhaseCarry* carry;
 };
 
 // The phase runs on one CU, so it is bound by the latency of its chain for small particles and
@@ -1000,7 +1026,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             }
         }
     }
-    // per-wave partials, then thread 0 (the only user) adds them in wave order
+    // per-wave partials, then the first wave adds them in wave order
 #pragma unroll
     for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
     nb = wave_isum(nb);
@@ -1012,19 +1038,25 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         shi[1][tid >> 6] = flags;
     }
     __syncthreads();
-    if (tid == 0) {
+    if (tid < 64) {
+        // lane k adds the waves' partials of sum k in wave order; thread 0 collects the six
+        const int k = min(tid, 5);
+        double sum = shd[k][0];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            double sum = shd[k][0];
-#pragma unroll
-            for (int u = 1; u < NW; ++u) sum += shd[k][u];
-            acc[k] = sum;
-        }
+        for (int u = 1; u < NW; ++u) sum += shd[k][u];
         nb = shi[0][0];
         flags = shi[1][0];
+#pragma unroll
         for (int u = 1; u < NW; ++u) {
             nb += shi[0][u];
             flags |= shi[1][u];
+        }
+        const uint64_t bits = __builtin_bit_cast(uint64_t, sum);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, q);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), q);
+            acc[q] = __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
         }
     }
     // ---- wall force (eq 12), totals and the rigid-body update (eq 13-16) --------------
@@ -1083,23 +1115,46 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         const int64_t kk = step - a.trace_start;
         if (a.trace && kk >= 0 && kk < a.trace_cap) a.trace[kk] = rec;
         if (fl) atomicOr(a.flags, fl);
-        shd[0][0] = nxc;
-        shd[1][0] = nyc;
-        shd[2][0] = nth;
+        shd[6][0] = nxc;
+        shd[6][1] = nyc;
+        shd[6][2] = nth;
+        if (MODE == 0 && c.carry) {
+            PhaseCarry& y = *c.carry;
+            y.xc1 = xc;
+            y.yc1 = yc;
+            y.th1 = th;
+            y.ux1 = ux;
+            y.uy1 = uy;
+            y.om1 = om;
+            y.xc = nxc;
+            y.yc = nyc;
+            y.th = nth;
+            y.ux = nux;
+            y.uy = nuy;
+            y.om = nom;
+            y.step = step + 1;
+        }
     }
+    if (MODE == 0 && a.no_predict) return true;
     __syncthreads();
 
     // ---- the box of the next step (the sweep of the nodes outside it may then run while
     // the next particle phase does) -------------------------------------------------------
     if (MODE == 0) {
-        const double nxc = shd[0][0], nyc = shd[1][0], nth = shd[2][0];
+        const double nxc = shd[6][0], nyc = shd[6][1], nth = shd[6][2], ncth = cos(nth), nsth = sin(nth);
         MarkerSet<MPT> Gn;
-        marker_set<MPT>(c.D, a.nl, a.ny, nxc, nyc, cos(nth), sin(nth), Gn);
-        int rn[4] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff};
-        set_bounds<MPT>(Gn, a.ny, rn);
-        const int op[4] = {2, 2, 2, 2};
-        block_int<4>(rn, op, shi);
+        marker_set<MPT>(c.D, a.nl, a.ny, nxc, nyc, ncth, nsth, Gn);
+        int rn[5];
+        box_bounds<MPT>(Gn, c.D, a, shi, rn);
         if (tid == 0) {
+            if (c.carry) {
+                PhaseCarry& y = *c.carry;
+                y.cth = ncth;
+                y.sth = nsth;
+#pragma unroll
+                for (int k = 0; k < 5; ++k) y.r[k] = rn[k];
+                y.valid = 1;
+            }
             const int nw = (rn[0] != 0x7fffffff) ? -rn[1] - rn[0] + 1 : 0;
             const int nh = (rn[2] != 0x7fffffff) ? -rn[3] - rn[2] + 1 : 0;
             TileDesc z;
@@ -1137,7 +1192,11 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     constexpr int stride = map_stride(MODE);
     int* nodes = stride == 2 ? (int*)B.fx : (int*)(base + 5 * m);
     c.nodes = nodes;
-    write_node_map<stride>(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
+    if (c.whole) {
+        if ((int)threadIdx.x < m) nodes[(int)threadIdx.x * stride] = (int)threadIdx.x;
+    } else {
+        write_node_map<stride>(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
+    }
     __syncthreads();
     return phase_body<T, MPT, LDS, MODE>(a, c, B, ov, nov, shd, shi);
 }
@@ -1154,7 +1213,7 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
 // shd, shi: the workgroup's reduction scratch in LDS.
 template <typename T, int MPT, int MODE>
 __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes,
-                                               double (*shd)[NW], int (*shi)[NW])
+                                               double (*shd)[NW], int (*shi)[NW], PhaseCarry* carry = nullptr)
 {
     const int tid = threadIdx.x;
     OvEntry* ov = (OvEntry*)lds;
@@ -1187,34 +1246,43 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     TileDesc zin{};  // the box the previous step predicted for this one (thread 0)
     if (MODE == 0 && a.check_zone && tid == 0) zin = a.zone[a.parity_in];
     c.zin = zin;
-    const DevParticle* st = a.st;
-    c.xc = st->xc;
-    c.yc = st->yc;
-    c.th = st->th;
-    c.ux = st->ux;
-    c.uy = st->uy;
-    c.om = st->om;
-    c.step = st->step;
-    c.xc1 = st->xc1;
-    c.yc1 = st->yc1;
-    c.th1 = st->th1;
-    c.ux1 = st->ux1;
-    c.uy1 = st->uy1;
-    c.om1 = st->om1;
-    c.cth = cos(c.th);
-    c.sth = sin(c.th);
+    c.carry = carry;
+    const bool carried = carry && carry->valid;
+    auto load_state = [&](const auto* st) {
+        c.xc = st->xc;
+        c.yc = st->yc;
+        c.th = st->th;
+        c.ux = st->ux;
+        c.uy = st->uy;
+        c.om = st->om;
+        c.step = st->step;
+        c.xc1 = st->xc1;
+        c.yc1 = st->yc1;
+        c.th1 = st->th1;
+        c.ux1 = st->ux1;
+        c.uy1 = st->uy1;
+        c.om1 = st->om1;
+    };
+    if (carried) {
+        load_state(carry);
+        c.cth = carry->cth;
+        c.sth = carry->sth;
+    } else {
+        load_state((const DevParticle*)a.st);
+        c.cth = cos(c.th);
+        c.sth = sin(c.th);
+    }
     c.flags = 0;
     marker_set<MPT>(c.D, a.nl, a.ny, c.xc, c.yc, c.cth, c.sth, c.G);
 
     // ---- the box: every node a marker or probe support reaches this step --------------
     // (and the ligands within y_cr of the wall, which the bond draws need)
-    int r[5] = {0x7fffffff, 0x7fffffff, 0x7fffffff, 0x7fffffff, 0};
-    set_bounds<MPT>(c.G, a.ny, r);
+    int r[5];
+    if (carried) {
 #pragma unroll
-    for (int k = 0; k < MPT; ++k) r[4] += c.D.lig[k] && c.G.Y[k] + 0.5 < a.y_cr ? 1 : 0;
-    {
-        const int op[5] = {2, 2, 2, 2, 0};
-        block_int<5>(r, op, shi);
+        for (int k = 0; k < 5; ++k) r[k] = __builtin_amdgcn_readfirstlane(carry->r[k]);
+    } else {
+        box_bounds<MPT>(c.G, c.D, a, shi, r);
     }
     c.nprobe = r[4];
     c.x0 = r[0];
@@ -1253,12 +1321,25 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     double* fields = (double*)(pre + nw);  // 8-byte aligned: head and 8 nw are multiples of 8
     const size_t aux = head + (size_t)nw * 8;
     const int lds_slots = lds_bytes > aux ? (int)((lds_bytes - aux) / slot_bytes(MODE)) : 0;
-    for (int k = tid; k < nw; k += PB) mask[k] = 0u;
-    __syncthreads();
-    if (c.box_ok)
-        mark_windows<MPT>(c.G, a.ny, (MODE == 0 || MODE == 4) ? 3 : MODE == 1 ? 1 : 2, c.x0, c.y0, c.w, c.h, mask);
-    __syncthreads();
-    c.nmarked = mask_prefix(mask, pre, nw, shi);
+    // A box of at most a node per thread is taken whole: every node of it costs the fill no more
+    // than the marked ones, and the marks, their prefix and the map are not needed (2.2 us of 16
+    // for a box of 16 x 14 nodes).  A node that no support reaches gets a zero force.
+    c.whole = c.nbox <= PB;
+    if (c.whole) {
+        if (tid < nw) {
+            mask[tid] = c.nbox - 32 * tid >= 32 ? ~0u : (1u << (c.nbox - 32 * tid)) - 1u;
+            pre[tid] = 32 * tid;
+        }
+        c.nmarked = c.nbox;
+        __syncthreads();
+    } else {
+        for (int k = tid; k < nw; k += PB) mask[k] = 0u;
+        __syncthreads();
+        if (c.box_ok)
+            mark_windows<MPT>(c.G, a.ny, (MODE == 0 || MODE == 4) ? 3 : MODE == 1 ? 1 : 2, c.x0, c.y0, c.w, c.h, mask);
+        __syncthreads();
+        c.nmarked = mask_prefix(mask, pre, nw, shi);
+    }
     c.mask = mask;
     c.pre = pre;
     const int nov = MODE == 2 ? overlap_list(a, rq, dq, c.x0, c.y0, c.w, c.h, ov, shi) : 0;
@@ -1276,11 +1357,12 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
 }
 
 template <typename T, int MPT, int MODE>
-__device__ __forceinline__ void particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes)
+__device__ __forceinline__ void particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes,
+                                               PhaseCarry* carry = nullptr)
 {
     __shared__ double shd[8][NW];
     __shared__ int shi[8][NW];
-    (void)particle_phase<T, MPT, MODE>(a, lds, lds_bytes, shd, shi);
+    (void)particle_phase<T, MPT, MODE>(a, lds, lds_bytes, shd, shi, carry);
 }
 
 template <typename T, int MPT>
@@ -1308,6 +1390,7 @@ constexpr size_t kRunStageBytes = 768;
 static_assert(sizeof(RunStage<double>) <= kRunStageBytes && sizeof(RunStage<half_neq_t>) <= kRunStageBytes,
               "the run's arguments fit their LDS copy");
 __shared__ __align__(16) unsigned char run_stage[kRunStageBytes];
+__shared__ PhaseCarry run_carry;
 
 template <typename T, int MPT>
 __device__ __noinline__ void run_step(int32_t k_in)
@@ -1344,7 +1427,7 @@ __device__ __noinline__ void run_step(int32_t k_in)
     a.zone_tag = (uint32_t)(a.ready_value & 0xffffu);
     a.zdone_target += (unsigned long long)k * (unsigned long long)run.nzone;
     if (k > 0) a.check_prev = a.pair_first ? 2 : 1;
-    particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes);
+    particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes, &run_carry);
 }
 
 template <typename T, int MPT>
@@ -1355,6 +1438,7 @@ __global__ __launch_bounds__(PB) void particle_run_kernel(ParticleArgs<T> a, Par
         sg.a = a;
         sg.run = run;
         sg.lds_bytes = lds_bytes;
+        run_carry.valid = 0;
     }
     __syncthreads();
     for (int32_t k = 0; k < run.nsteps; ++k) {
@@ -1557,7 +1641,7 @@ __global__ __launch_bounds__(PB) void pool_particle_kernel(const ParticleArgs<T>
 {
     extern __shared__ double lds_dyn[];
     const int k = active[blockIdx.x];
-    TileDesc* const c = ctl + (half ? (int)gridDim.x + k : k);
+    TileDesc* const c = ctl + (half == 1 ? (int)gridDim.x + k : k);
     ParticleArgs<T> a = args[k];
     const int64_t n = a.st->step;
     if (n >= a.target_steps || *a.flags != 0) {
@@ -1566,7 +1650,8 @@ __global__ __launch_bounds__(PB) void pool_particle_kernel(const ParticleArgs<T>
     }
     const int buf = a.st->buf;
     a.f = buf ? a.fB : a.f;
-    if (half) {
+    a.no_predict = half != 0;  // only a first half's prediction is read, by the zone launch
+    if (half == 1) {
         a.tile = sims[k].tile_b;
         a.ring = sims[k].ring_b;
         a.parity_in = 1;
@@ -1578,7 +1663,7 @@ __global__ __launch_bounds__(PB) void pool_particle_kernel(const ParticleArgs<T>
         TileDesc d = coherent_load(a.desc);
         d.pad = buf;
         *c = d;
-        if (!half) a.st->buf = buf ^ 1;
+        if (half != 1) a.st->buf = buf ^ 1;
     }
 }
 

@@ -355,8 +355,9 @@ hipError_t launch_steps(lbib_pool* h, int64_t n)
     const PoolSweep<T>* sims = (const PoolSweep<T>*)h->d_sims;
     hipError_t e = hipSuccess;
     while (n > 0 && e == hipSuccess) {
-        if ((e = launch_half<T>(h, 0)) != hipSuccess) break;
-        if (h->pairs && n >= 2) {
+        const bool pair = h->pairs && n >= 2;
+        if ((e = launch_half<T>(h, pair ? 0 : 2)) != hipSuccess) break;
+        if (pair) {
             if ((e = launch_pool_zone<T>(sims, h->d_ctl, h->n_active, h->stream)) != hipSuccess) break;
             if ((e = launch_half<T>(h, 1)) != hipSuccess) break;
             const EvPair e0 = next_events(h, 0, 2);

@@ -89,11 +89,7 @@ lbib_status enqueue_solve(const LatticeGeom& g, uint64_t seed, Particle& p, int6
         pa.parity_in = par;
         pa.parity_out = par ^ 1;
         pa.check_zone = 0;
-        // the hand-over words are written as in lbib_step's serial steps (nothing waits on them)
-        pa.ready = p.d_count;
-        pa.ready_value = (unsigned long long)step + 1;
-        pa.zone_words = p.d_count + 2 + 2 * ((step + 1) & 3);
-        pa.zone_tag = (uint32_t)((step + 1) & 0xffff);
+        pa.no_predict = 1;
         SCHK(launch_particle<T>(pa, s));
         SCHK(launch_sweep<T>((const T*)fA, (T*)fB, sa, p.d_desc, p.d_tile, p.d_ring, g.pull, s, nullptr, nullptr,
                              reverse_sweep(g, step)));
