@@ -327,6 +327,18 @@ hipError_t launch_particle(const ParticleArgs<T>& a, hipStream_t stream, hipEven
 // reads the level the last sweep left, the second its zone in the buffer that sweep will
 // overwrite (so the buffers of four steps are even, odd, odd, even), and leaves its force in
 // tile_b, ring_b and desc_b.
+// help (or NULL; the f - f_eq storages): the run is launched with kHelpers more workgroups, which
+// fill the node fields of its steps (HelpArea).
+constexpr int kHelpers = 8;
+constexpr int kHelpMarkers = 384;  // the particle that has them (lbib_particle.hip: HelpStep)
+constexpr int kHelpNodes = 4096;  // as many as LDS can hold node fields of
+struct HelpArea {
+    unsigned long long msg[8];      // the pose a step starts from: six tagged half words
+    unsigned long long arrived[8];  // the run a helper has started in, by its first ready value
+    unsigned long long done[8];     // the last step a helper has filled, by its ready value
+    double mom[3][kHelpNodes];      // density and velocity of the marked nodes, by slot
+};
+static_assert(kHelpers <= 8, "a word of HelpArea each");
 template <typename T>
 struct ParticleRun {
     const T* f_even;
@@ -339,6 +351,7 @@ struct ParticleRun {
     int64_t* tile_b;
     uint2* ring_b;
     TileDesc* desc_b;
+    HelpArea* help;
 };
 template <typename T>
 hipError_t launch_particle_run(const ParticleArgs<T>& a, const ParticleRun<T>& run, hipStream_t stream,

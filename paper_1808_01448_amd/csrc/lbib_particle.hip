@@ -732,8 +732,160 @@ struct PhaseCarry {
     double xc, yc, th, ux, uy, om, xc1, yc1, th1, ux1, uy1, om1, cth, sth;
     int64_t step;
     int32_t r[5];
-    int32_t valid;
+    int32_t valid;    // 1: all of it; 2: the pose alone (a helper)
+    int32_t present;  // every helper of the run has started
+    int32_t use;      // the helpers fill the next step's node fields
 };
+
+// A step of a resident launch with helpers.  One CU draws the lines of a large particle's nodes
+// at 2 ns each, and at 3 to 4 ns beside a sweep that fills the memory.  The f - f_eq storages
+// take 18 loads a node, two nodes a lane in flight: 14.0 us of a phase of 40.6 alone and 34.0 of
+// 62.6 beside the sweep for 640 markers in 2999 x 777.  kHelpers more workgroups of the launch, each on a CU of its own, take that gather: the leader
+// sends the pose a step starts from as soon as its update has it; each helper marks and maps the
+// nodes for itself (the same operations on the same values: the same slots), waits for the
+// sweep's zone workgroups, evaluates density and velocity at its share of the slots and counts
+// in; the leader reads three values per node, in slot order.
+//   The leader never depends on a helper that has not started: it fills its nodes itself until
+// all have (arrived), so a helper that finds no room beside other work costs speed alone.  It
+// sends a pose only once every helper has counted in for the previous one, so none is missed.
+//   us per step alone -> helped, stored as f - f_eq: 384 markers (512 x 400) 31.6 -> 30.1, 576
+// (2048 x 600) 48.1 -> 40.5, 640 (2999 x 777) 62.8 -> 50.5, 832 (2048 x 900) 67.1 -> 47.8.  The
+// hand-over costs about as much as the whole fill of the other storages (832 markers FP32 40.2 ->
+// 45.0, FP64 49.6 -> 50.7), so only these have it (kHelped), from kHelpMarkers.
+struct HelpStep {
+    HelpArea* area;  // NULL: a launch without helpers
+    int32_t me;      // 0: the leader
+    bool use;
+    int32_t next, nsteps;      // of the run: the step after this one, and how many there are
+    unsigned long long base;   // ready value of the run's first step
+};
+template <typename T>
+constexpr bool kHelped = St<T>::neq;
+// A pose's tag: the step's ready value (31 bits) and whether the helpers are to fill it.
+__device__ __forceinline__ uint32_t help_tag(const HelpStep& s, int32_t k, bool use)
+{
+    return ((uint32_t)(s.base + (unsigned long long)k) << 1) | (use ? 1u : 0u);
+}
+// The leader's thread 0, with the pose of step s.next.  The words carry their tag, so they need
+// no order and no flag.  The pose after the run's last step, which nobody fills, ends the helpers.
+__device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, double x, double yy, double th)
+{
+    if (!y.present) {
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < kHelpers; ++k)
+            all &= (unsigned long long)coherent_load((const int64_t*)s.area->arrived + k) == s.base;
+        y.present = all;
+    }
+    const bool use = y.present && s.next < s.nsteps;
+    y.use = use;
+    if (!use && s.next < s.nsteps) return;
+    const unsigned long long tag = (unsigned long long)help_tag(s, s.next, use) << 32;
+    const double v[3] = {x, yy, th};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const unsigned long long b = (unsigned long long)__double_as_longlong(v[k]);
+        coherent_store((int64_t*)s.area->msg + 2 * k, (int64_t)(tag | (b & 0xffffffffull)));
+        coherent_store((int64_t*)s.area->msg + 2 * k + 1, (int64_t)(tag | (b >> 32)));
+    }
+}
+// A helper's first wave: polls for the next pose to fill, leaves it in y and returns its step, or
+// the run's length once the run has ended (or its hand-over has failed).  Not bounded by itself,
+// since a leader that fills alone sends nothing for the whole run: the leader is dispatched first
+// and all its waits are bounded, so it reaches the end of its run and sends the last pose.
+__device__ __forceinline__ int32_t help_receive(HelpArea* area, unsigned long long base, int32_t nsteps, int32_t* flags,
+                                                PhaseCarry& y)
+{
+    const int lane = threadIdx.x & 63;
+    for (unsigned polls = 0;; ++polls) {
+        const unsigned long long m =
+            lane < 6 ? (unsigned long long)coherent_load((const int64_t*)area->msg + lane) : 0ull;
+        const uint32_t hi = (uint32_t)(m >> 32), lo = (uint32_t)m;
+        const uint32_t tag = __builtin_amdgcn_readfirstlane(hi);
+        const uint32_t k = ((tag >> 1) - (uint32_t)base) & 0x7fffffffu;
+        if (__all(lane >= 6 || hi == tag) && k >= 1 && k <= (uint32_t)nsteps && ((tag & 1u) || k == (uint32_t)nsteps)) {
+            double v[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                v[q] = __longlong_as_double(
+                    (int64_t)(((unsigned long long)(uint32_t)__builtin_amdgcn_readlane(lo, 2 * q + 1) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane(lo, 2 * q)));
+            if (lane == 0) {
+                y.xc = v[0];
+                y.yc = v[1];
+                y.th = v[2];
+                y.valid = 2;
+            }
+            return (int32_t)k;
+        }
+        if ((polls & 255u) == 0 && (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & FLAG_SYNC))
+            return nsteps;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+// The leader's first wave: waits until every helper has filled its share of this step (bounded,
+// as wait_counter).
+__device__ __forceinline__ void help_wait(const HelpArea* area, unsigned long long step, int32_t* flags)
+{
+    const int lane = threadIdx.x & 63;
+    for (unsigned polls = 0;; ++polls) {
+        const bool ok =
+            lane >= kHelpers || (unsigned long long)coherent_load((const int64_t*)area->done + lane) == step;
+        if (__all(ok)) return;
+        if ((polls & 255u) == 0 && (__hip_atomic_load(flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & FLAG_SYNC))
+            return;
+        if (polls > (1u << 20)) {
+            if (lane == 0) atomicOr(flags, FLAG_SYNC);
+            return;
+        }
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+// A helper's share of the fill.
+template <typename T>
+__device__ __forceinline__ void help_fill(const ParticleArgs<T>& a, const HelpStep& s, const int* nodes, int stride, int nm,
+                                          int x0, int y0, int w)
+{
+    const BoxDiv bd = box_div(w);
+    const int xw = wrap(x0, a.nx);
+    const int per = (nm + 64 * kHelpers - 1) / (64 * kHelpers) * 64;
+    const int lo = (s.me - 1) * per, hi = min(nm, lo + per);
+    for (int sl = lo + (int)threadIdx.x; sl < hi; sl += PB) {
+        int row, col;
+        box_node(bd, nodes[sl * stride], row, col);
+        int i = xw + col;
+        if (i >= a.nx) i -= a.nx;
+        double v[9], dr, jx, jy;
+        load_node<T, double>(a.f, i, y0 + row, a.nx, a.ny, a.pitch, a.plane, a.pull != 0, a.inv_scale, a.uw6, false, v);
+        shifted_moments<double, double>(v, dr, jx, jy);
+        const double rho = 1.0 + dr;
+        const double inv = 1.0 / rho;
+        state_store(&s.area->mom[0][sl], rho);
+        state_store(&s.area->mom[1][sl], (jx + 0.5 * a.gx) * inv);
+        state_store(&s.area->mom[2][sl], (jy + 0.5 * a.gy) * inv);
+    }
+}
+// The leader's: three values per node, four nodes per lane in flight.
+__device__ __forceinline__ void help_read(const HelpArea* area, const NodeView& B, int nm)
+{
+    for (int s0 = (int)threadIdx.x; s0 < nm; s0 += 4 * PB) {
+        int64_t v[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                v[u][k] = coherent_load((const int64_t*)area->mom[k] + min(s0 + u * PB, nm - 1));
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int sl = s0 + u * PB;
+            if (sl >= nm) break;
+            B.rho[sl] = __longlong_as_double(v[u][0]);
+            B.ux[sl] = __longlong_as_double(v[u][1]);
+            B.uy[sl] = __longlong_as_double(v[u][2]);
+            B.fx[sl] = B.fy[sl] = 0ull;
+        }
+    }
+}
 
 // What the first part of the particle phase hands to the rest.
 template <int MPT>
@@ -750,6 +902,8 @@ struct PhaseCtx {
     MarkerData<MPT> D;
     TileDesc zin;
     PhaseCarry* carry;
+    HelpStep help;
+    bool helped;  // (the leader) this step's node fields come from the helpers
 };
 
 // The phase runs on one CU, so it is bound by the latency of its chain for small particles and
@@ -777,8 +931,11 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
     int flags = c.flags;
     DevParticle* st = a.st;
 
-    fill_nodes<T, MODE == 2, fill_nodes_per_lane<T>(MODE), map_stride(MODE)>(a, B, c.nodes, c.nmarked, x0, y0, w, ov,
-                                                                             nov);
+    if (kHelped<T> && MODE == 0 && c.carry && c.helped)
+        help_read(c.help.area, B, c.nmarked);
+    else
+        fill_nodes<T, MODE == 2, fill_nodes_per_lane<T>(MODE), map_stride(MODE)>(a, B, c.nodes, c.nmarked, x0, y0, w,
+                                                                                 ov, nov);
     __syncthreads();
 
     // ---- markers: MLS interpolation and direct forcing ----------------------------------
@@ -1076,6 +1233,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         const double nth = (2.0 / 3.0) * (2.0 * th - 0.5 * c.th1 + nom);
         if (!(isfinite(Fx) && isfinite(Fy) && isfinite(M) && isfinite(nux) && isfinite(nuy) && isfinite(nom)))
             fl |= FLAG_NONFINITE;
+        if (kHelped<T> && MODE == 0 && c.carry && c.help.area) help_send(c.help, *c.carry, nxc, nyc, nth);
         // the state the next step starts from, stored coherently (as the bond flags)
         state_store(&st->xc1, xc);
         state_store(&st->yc1, yc);
@@ -1183,8 +1341,10 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
 template <typename T, int MPT>
 __device__ __forceinline__ void zone_wait(const ParticleArgs<T>& a, PhaseCtx<MPT>& c)
 {
-    wait_counter(a.zdone, a.zdone_target, a.flags);
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (!c.helped) {
+        wait_counter(a.zdone, a.zdone_target, a.flags);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
     if (a.check_prev && c.box_ok) {
         // those workgroups covered the previous box (of the last two steps swept together,
         // the first's) widened by kZoneMargin: this box must lie in it widened by
@@ -1216,13 +1376,23 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     constexpr int stride = map_stride(MODE);
     int* nodes = stride == 2 ? (int*)B.fx : (int*)(base + 5 * m);
     c.nodes = nodes;
-    if (c.whole) {
+    constexpr bool can_help = kHelped<T> && MODE == 0;  // (and a resident launch's: carry)
+    const bool share = LDS && m <= kHelpNodes;  // the leader's and the helpers' verdicts agree
+    c.helped = can_help && c.carry && c.help.use && c.help.me == 0 && share;
+    if (c.helped) {
+    } else if (c.whole) {
         if ((int)threadIdx.x < m) nodes[(int)threadIdx.x * stride] = (int)threadIdx.x;
     } else {
         write_node_map<stride>(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
     }
     if (MODE == 0 && a.zdone && threadIdx.x == 0) zone_wait(a, c);
+    if (can_help && c.carry && c.help.use && c.help.me == 0 && threadIdx.x < 64)
+        help_wait(c.help.area, c.help.base + (unsigned long long)(c.help.next - 1), a.flags);
     __syncthreads();
+    if (can_help && c.carry && c.help.me != 0) {
+        if (share) help_fill(a, c.help, nodes, stride, m, c.x0, c.y0, c.w);
+        return true;
+    }
     return phase_body<T, MPT, LDS, MODE>(a, c, B, ov, nov, shd, shi);
 }
 
@@ -1238,7 +1408,8 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
 // shd, shi: the workgroup's reduction scratch in LDS.
 template <typename T, int MPT, int MODE>
 __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes,
-                                               double (*shd)[NW], int (*shi)[NW], PhaseCarry* carry = nullptr)
+                                               double (*shd)[NW], int (*shi)[NW], PhaseCarry* carry = nullptr,
+                                               const HelpStep& help = HelpStep{})
 {
     const int tid = threadIdx.x;
     OvEntry* ov = (OvEntry*)lds;
@@ -1272,7 +1443,10 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     if (MODE == 0 && a.check_zone && tid == 0) zin = a.zone[a.parity_in];
     c.zin = zin;
     c.carry = carry;
-    const bool carried = carry && carry->valid;
+    c.help = help;
+    c.helped = false;
+    const int valid = carry ? __builtin_amdgcn_readfirstlane(carry->valid) : 0;
+    const bool carried = valid == 1;
     auto load_state = [&](const auto* st) {
         c.xc = st->xc;
         c.yc = st->yc;
@@ -1292,6 +1466,10 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
         load_state(carry);
         c.cth = carry->cth;
         c.sth = carry->sth;
+    } else if (valid == 2) {
+        load_state(carry);  // (a helper uses the pose alone)
+        c.cth = cos(c.th);
+        c.sth = sin(c.th);
     } else {
         load_state((const DevParticle*)a.st);
         c.cth = cos(c.th);
@@ -1360,11 +1538,11 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
 
 template <typename T, int MPT, int MODE>
 __device__ __forceinline__ void particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes,
-                                               PhaseCarry* carry = nullptr)
+                                               PhaseCarry* carry = nullptr, const HelpStep& help = HelpStep{})
 {
     __shared__ double shd[8][NW];
     __shared__ int shi[8][NW];
-    (void)particle_phase<T, MPT, MODE>(a, lds, lds_bytes, shd, shi, carry);
+    (void)particle_phase<T, MPT, MODE>(a, lds, lds_bytes, shd, shi, carry, help);
 }
 
 template <typename T, int MPT>
@@ -1424,12 +1602,14 @@ __device__ __noinline__ void run_step(int32_t k_in)
     }
     a.parity_in = (int32_t)(step & 1);
     a.parity_out = a.parity_in ^ 1;
+    const bool use = kHelped<T> && run.help && (blockIdx.x != 0 || __builtin_amdgcn_readfirstlane(run_carry.use) != 0);
+    const HelpStep help{run.help, kHelped<T> ? (int32_t)blockIdx.x : 0, use, k + 1, run.nsteps, a.ready_value};
     a.ready_value += (unsigned long long)k;
     a.zone_words = run.zone_base + 2 * ((step + 1) & 3);
     a.zone_tag = (uint32_t)(a.ready_value & 0xffffu);
     a.zdone_target += (unsigned long long)k * (unsigned long long)run.nzone;
     if (k > 0) a.check_prev = a.pair_first ? 2 : 1;
-    particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes, &run_carry);
+    particle_phase<T, MPT, 0>(a, (char*)lds_dyn, lds_bytes, &run_carry, help);
 }
 
 template <typename T, int MPT>
@@ -1440,9 +1620,28 @@ __global__ __launch_bounds__(PB) void particle_run_kernel(ParticleArgs<T> a, Par
         sg.a = a;
         sg.run = run;
         sg.lds_bytes = lds_bytes;
-        run_carry.valid = 0;
+        run_carry.valid = run_carry.present = run_carry.use = 0;
     }
     __syncthreads();
+    if (kHelped<T> && blockIdx.x != 0) {
+        if (threadIdx.x == 0)
+            coherent_store((int64_t*)run.help->arrived + (blockIdx.x - 1), (int64_t)a.ready_value);
+        for (;;) {
+            if (threadIdx.x < 64) {
+                const int32_t k = help_receive(run.help, a.ready_value, run.nsteps, a.flags, run_carry);
+                if (threadIdx.x == 0) run_carry.r[0] = k;
+            }
+            __syncthreads();
+            const int32_t k = __builtin_amdgcn_readfirstlane(run_carry.r[0]);
+            if (k >= run.nsteps) return;
+            run_step<T, MPT>(k);
+            stores_done();
+            __syncthreads();
+            if (threadIdx.x == 0)
+                coherent_store((int64_t*)run.help->done + (blockIdx.x - 1),
+                               (int64_t)(a.ready_value + (unsigned long long)k));
+        }
+    }
     for (int32_t k = 0; k < run.nsteps; ++k) {
         run_step<T, MPT>(k);
         __syncthreads();  // every wave is done with this step's LDS before the next step's writes
@@ -1727,8 +1926,8 @@ hipError_t launch_particle_run_mpt(const ParticleArgs<T>& a, const ParticleRun<T
     if (e != hipSuccess) return e;
     const size_t lds = particle_launch_lds(a.box_cap);
     if (particle_lds_aux_bytes(a.box_cap) > lds) return hipErrorInvalidValue;
-    hipExtLaunchKernelGGL(particle_run_kernel<T, MPT>, dim3(1), dim3(PB), (uint32_t)lds, stream, t0, t1, 0u, a, run,
-                          (uint32_t)lds);
+    hipExtLaunchKernelGGL(particle_run_kernel<T, MPT>, dim3(kHelped<T> && run.help ? 1 + kHelpers : 1), dim3(PB),
+                          (uint32_t)lds, stream, t0, t1, 0u, a, run, (uint32_t)lds);
     return hipGetLastError();
 }
 

@@ -50,6 +50,7 @@ struct lbib_sim {
     // two steps per sweep (PairHandover): the second step's force list, its index and its box
     bool pairs = false;
     char* d_pair = nullptr;
+    HelpArea* d_help = nullptr;  // the helpers of the resident particle launch (NULL: none)
     int64_t* d_tile_b = nullptr;
     uint2* d_ring_b = nullptr;
     TileDesc* d_desc_b = nullptr;
@@ -167,6 +168,7 @@ void free_all(lbib_sim* h)
     dfree(h->stage.p);
     h->stage.bytes = 0;
     dfree(h->d_pair);
+    dfree(h->d_help);
     h->pairs = false;
     dfree(h->d_masks);
     dfree(h->d_bar);
@@ -460,7 +462,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
                     if (run_left == 0) {
                         const int64_t len = std::min<int64_t>(n - s, kRunSteps);
                         const ParticleRun<T> run{fin,   (const T*)h->fB, p.d_count + 2, h->steps,    (int32_t)len,
-                                                 nzone, pairs ? 1 : 0,   h->d_tile_b,   h->d_ring_b, h->d_desc_b};
+                                                 nzone, pairs ? 1 : 0,   h->d_tile_b,   h->d_ring_b, h->d_desc_b, h->d_help};
                         const EvPair e1 = timing_events(h, 1, len);
                         HIPCHK(h, launch_particle_run<T>(pa, run, h->stream2, e1.t0, e1.t1));
                         run_left = len;
@@ -758,6 +760,16 @@ lbib_status lbib_init(lbib_handle h)
             (void)hipGetLastError();
             h->d_pair = nullptr;
             h->pairs = false;
+        }
+    }
+    if (h->parts.size() == 1 && h->parts[0].nl >= kHelpMarkers && h->g.neq) {
+        e = hipMalloc((void**)&h->d_help, sizeof(HelpArea));
+        if (e == hipSuccess) {
+            if ((e = hipMemsetAsync(h->d_help, 0, sizeof(HelpArea), h->stream)) != hipSuccess)
+                return bail(e, "lbib_init: helpers");
+        } else {  // no room: the particle phase fills its nodes alone
+            (void)hipGetLastError();
+            h->d_help = nullptr;
         }
     }
     if ((e = hipStreamCreateWithFlags(&h->stream2, hipStreamNonBlocking)) != hipSuccess)

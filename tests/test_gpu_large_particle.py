@@ -1,6 +1,6 @@
-"""GPU: particles whose box has more mask words than a round of the node map takes, with the
-node fields in LDS and, for the widest marker spacing, in the global scratch; against the FP64
-oracle, in both layouts and schedules."""
+"""GPU: particles whose box has about a node per thread, and particles whose box has more mask
+words than a round of the node map takes, with the node fields in LDS and, for the widest marker
+spacing, in the global scratch; against the FP64 oracle, in both layouts and schedules."""
 import numpy as np
 import pytest
 
@@ -9,6 +9,8 @@ from paper_1808_01448_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
+    # boxes on both sides of a node per thread (512): taken whole, and marked and mapped
+    **{f"whole_{r}": dict(a_major=r, b_minor=r, n_markers=64, shape=0) for r in (8.0, 8.4, 8.8, 9.2, 9.6)},
     # box 4100 nodes: the last that the map takes by half-waves, and the first beyond
     "words_128": dict(a_major=30.0, b_minor=30.0, n_markers=192, shape=0),
     "words_129": dict(a_major=30.5, b_minor=30.5, n_markers=192, shape=0),
