@@ -6,9 +6,10 @@ sweep) on the 4096 x 1024 FP32 channel with one aspect-ratio-3 ellipse (256 mark
 ligand density 0.7, bond strength 2, Re 1), inputs resident in HBM.  Prints one JSON line:
 whole-step throughput in MLUPS over the K timed steps (host clock, bracketed by device
 synchronisations; HIP events on the simulation's stream beside it, and a 1000-step window
-that shows the fixed cost of a call), the lattice sweep's roofline (algorithmic bytes per
-launch over its HIP-event-timed average duration, against the 8 TB/s HBM peak and the
-measured copy), the same sweep on an 8192 x 4096 channel far beyond the 256 MB last-level
+that shows the fixed cost of a call), the lattice sweep's roofline (the bytes that one pass
+over the populations reads and writes, over the HIP-event-timed average duration of a
+launch, against the 8 TB/s HBM peak and the measured copy; a launch that takes two steps in
+its pass moves those bytes once), the same sweep on an 8192 x 4096 channel far beyond the 256 MB last-level
 cache in every storage precision, the 256 x 64 FP64 channel (latency-bound), the
 216-simulation parameter sweep (pool against the plain loops), 32 particles in one channel,
 the serving mix, and the FP64 CPU oracle timed on this host's cores and on one thread.
@@ -31,7 +32,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_sweep_4096x1024_fp32.json
 TRAFFIC_FILE_BEYOND = os.path.join(ROOT, "profiles", "traffic_sweep_8192x4096_storages.json")
 # the lattice sweep's device code: the counters in the traffic files are valid for these sources only
 KERNEL_SRCS = [os.path.join(ROOT, "paper_1808_01448_amd", "csrc", f)
-               for f in ("lbib_sweep.hip", "lbib_collide.hpp", "lbib_device.hpp", "lbib_internal.hpp")]
+               for f in ("lbib_sweep.hip", "lbib_march.hpp", "lbib_collide.hpp", "lbib_device.hpp")]
 LEGS = ("beyond", "c1", "batched", "multi", "serve", "cpu")
 
 
@@ -144,8 +145,16 @@ STORAGE_TYPE = {"fp32": "float", "fp64": "double", "fp16": "half_t", "bf16": "bf
                 "bf16_neq": "bf16_neq_t"}
 
 
-def sweep_kernel_name(prec: str, serial: bool) -> str:
-    return ("sweep_kernel" if serial else "sweep_overlap_kernel") + f"<{STORAGE_TYPE[prec]}, push>"
+def steps_per_sweep(prec: str, traffic: float, serial: bool, least: float = 16e6) -> int:
+    """Steps that one sweep launch takes, by the library's rule: two from `least` bytes of
+    traffic per step (16 MB for one simulation, 100 MB for a pool), but one for the f - f_eq
+    storages and in the serial schedule."""
+    return 1 if serial or prec.endswith("_neq") or traffic < least else 2
+
+
+def sweep_kernel_name(prec: str, serial: bool, per: int) -> str:
+    return (("sweep_kernel" if serial else "sweep_overlap_kernel" if per == 1 else "sweep_pair_kernel")
+            + f"<{STORAGE_TYPE[prec]}, push>")
 
 
 def beyond_cache_leg(steps: int, stream, serial: bool = False) -> dict:
@@ -176,16 +185,17 @@ def beyond_cache_leg(steps: int, stream, serial: bool = False) -> dict:
         finally:
             sim.close()
         copy_gbs = lbib.bandwidth_probe(buf, 10, stream=stream)
-        achieved = bpu * cells / (sweep_ms * 1e-3) / 1e9
+        per = steps_per_sweep(prec, bpu * cells, serial)  # sweep_ms: per step
+        achieved = bpu * cells / (per * sweep_ms * 1e-3) / 1e9
         out["storages"][prec] = {
             "bytes_per_update": bpu, "working_set_mb": round(bpu * cells / 1e6, 1),
             "mlups": round(cells * steps / win["seconds"] / 1e6, 1),
             "ms_per_step": round(win["seconds"] * 1e3 / steps, 4),
             "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": round(achieved / HBM_PEAK_GBS, 4), "kernel": sweep_kernel_name(prec, serial),
+                         "frac": round(achieved / HBM_PEAK_GBS, 4), "kernel": sweep_kernel_name(prec, serial, per), "steps_per_launch": per,
                          **measured_traffic_beyond(prec, cells),
                          "algorithmic_bytes_per_launch": bpu * cells,
-                         "avg_launch_us": round(sweep_ms * 1e3, 2), "launches_timed": n0,
+                         "avg_launch_us": round(per * sweep_ms * 1e3, 2), "launches_timed": n0 // per,
                          "copy_same_bytes_gbs": round(copy_gbs, 1),
                          "frac_of_measured_copy": round(achieved / copy_gbs, 4) if copy_gbs > 0 else None},
             "particle_launch_avg_us": round(part_ms * 1e3, 2),
@@ -193,7 +203,7 @@ def beyond_cache_leg(steps: int, stream, serial: bool = False) -> dict:
             "tile_order": ("the same every step" if prec.endswith("_neq")
                            else "reversed on odd steps: a sweep first reads the tiles the previous one wrote last"),
         }
-        log(f"bench: beyond cache {prec}: sweep {sweep_ms * 1e3:.1f} us = {achieved:.0f} GB/s "
+        log(f"bench: beyond cache {prec}: sweep {sweep_ms * 1e3:.1f} us per step, {per} a launch = {achieved:.0f} GB/s "
             f"({achieved / HBM_PEAK_GBS:.3f} of 8 TB/s, {achieved / copy_gbs:.3f} of the copy {copy_gbs:.0f} GB/s)")
     return out
 
@@ -249,7 +259,8 @@ def batched_leg(steps: int, stream) -> dict:
     tx, tpb, _ = pool["config"]
     graph = measure.pool_throughput(ws, steps, 20, stream=stream, config=(tx, tpb, 50))
     log(f"bench: pool with graph replay {graph['mlups']:.0f} MLUPS")
-    sweep_gbs = 72.0 * cells / (pool["sweep_avg_us"] * 1e-6) / 1e9
+    per = steps_per_sweep("fp32", 72.0 * cells, False, 100e6)
+    sweep_gbs = 72.0 * cells / (per * pool["sweep_avg_us"] * 1e-6) / 1e9
     return {
         "workload": "parameter sweep: 216 simulations (shape x ligand density x bond strength x Re x seed), "
                     "grids nx U[512,2048] x ny U[128,256], FP32, tau 0.8",
@@ -266,7 +277,8 @@ def batched_leg(steps: int, stream) -> dict:
         "pool_sweep_avg_us": round(pool["sweep_avg_us"], 2),
         "pool_particle_avg_us": round(pool["particle_avg_us"], 2),
         "pool_sweep_roofline": {"bound": "hbm", "achieved": round(sweep_gbs, 1), "peak": HBM_PEAK_GBS,
-                                "unit": "GB/s", "frac": round(sweep_gbs / HBM_PEAK_GBS, 4)},
+                                "unit": "GB/s", "frac": round(sweep_gbs / HBM_PEAK_GBS, 4),
+                                "steps_per_launch": per},
         "accuracy": "each pooled simulation bit-identical to its plain run",
     }
 
@@ -498,12 +510,14 @@ def main():
         kr = 1000
         log(f"bench: {kr} steps with HIP events on the sweep")
         sweep_ms, n0, part_ms = sweep_timing(sim, kr)
-        achieved = bpu * cells / (sweep_ms * 1e-3) / 1e9
+        per = steps_per_sweep("fp32", bpu * cells, args.serial_schedule)  # sweep_ms: per step
+        achieved = bpu * cells / (per * sweep_ms * 1e-3) / 1e9
         roofline = {
             "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), **measured_traffic(cells),
-            "kernel": sweep_kernel_name("fp32", args.serial_schedule), "algorithmic_bytes_per_launch": bpu * cells,
-            "avg_launch_us": round(sweep_ms * 1e3, 2), "launches_timed": n0,
+            "kernel": sweep_kernel_name("fp32", args.serial_schedule, per), "steps_per_launch": per,
+            "algorithmic_bytes_per_launch": bpu * cells,
+            "avg_launch_us": round(per * sweep_ms * 1e3, 2), "launches_timed": n0 // per,
             "timing": f"HIP events (hipExtLaunchKernelGGL) on the sweep's stream over {kr} steps after the "
                       f"timed windows",
             "frac_of_measured_copy": round(achieved / copy_gbs, 4) if copy_gbs > 0 else None,
@@ -516,8 +530,9 @@ def main():
                          if args.serial_schedule else
                          "particle phases and sweeps on two streams with no event between them, handing "
                          "over through device memory; one particle launch stays resident over a call's "
-                         "steps, and the sweep's box tiles are taken by workgroups at the head of its grid "
-                         "once the particle has published its spread force"),
+                         "steps, a sweep takes two steps in one pass over memory, and the nodes around the "
+                         "particle's box are taken by workgroups at the head of its grid once the particle "
+                         "has published the spread force of each of the two"),
         }
     p = sim.particle()
     sim.close()

@@ -656,9 +656,10 @@ __device__ __forceinline__ void total_forces(const ParticleArgs<T>& a, const Nod
 
 // Meeting point of the one-launch split phase, which assumes nothing about which of its
 // workgroups are resident together.  Workgroups claim particles (claim_particle), which the
-// counter at ctr + kClaimWord counts; here the workgroup barrier completes every wave's stores,
-// one thread releases them at device scope and counts this spread in at *ctr, then polls until
-// every spread of the launch has counted in (target).  It waits only while every particle is
+// counter at ctr + kClaimWord counts; here every wave waits for its stores, which are coherent,
+// and after the workgroup barrier one thread counts this spread in at *ctr, then polls until
+// every spread of the launch has counted in (target).  (A device-scope release of plain stores
+// writes back the XCD's whole L2.)  It waits only while every particle is
 // claimed: a claimer is running, so its spread will count in.  While a particle is unclaimed
 // (its workgroup may be waiting for a CU this one holds) it returns false at once, and the
 // caller spreads the unclaimed particles itself.  Its device-scope acquire invalidates the
@@ -672,13 +673,19 @@ constexpr int kClaimWords = 4;  // then one claim word per particle
 __device__ __forceinline__ bool claimed_barrier(unsigned long long* ctr, unsigned long long target, int& flags)
 {
     __shared__ int go;
+    stores_done();
     __syncthreads();
     if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         int ok = 1;
         unsigned polls = 0;
-        while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (__hip_atomic_load(ctr + kClaimWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+        for (;;) {
+            // both words of a poll in flight at once
+            const unsigned long long spreads = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long claims =
+                __hip_atomic_load(ctr + kClaimWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (spreads >= target) break;
+            if (claims < target) {
                 ok = 0;
                 break;
             }
@@ -909,10 +916,11 @@ struct PhaseCtx {
 // The phase runs on one CU, so it is bound by the latency of its chain for small particles and
 // by that CU's memory requests and instruction issue for large ones.  us of the serial launch
 // (FP64 but where said), before -> after the node fields were cut to 40 bytes, the spread force
-// left as a list and the reductions went to register permutes: 64 markers 18.3 -> 17.1, 192
-// 19.4 -> 17.7, 576 (FP16) 43.6 -> 38.1, 960 (111 x 321 box, 3272 nodes; LDS now holds them)
-// 103 -> 41.  What is left of the last: fill 13 (its lines come from beyond the L2 at 2 ns
-// each), interpolation and probes 4 each, spread 4, list 2.
+// left as a list, the reductions went to register permutes and a small box is taken whole: 64
+// markers 18.3 -> 15.3, 192 19.4 -> 17.7, 576 (FP16) 43.6 -> 38.1, 960 (111 x 321 box, 3272
+// nodes; LDS now holds them) 103 -> 43.  What is left of the last: fill 12 (its lines come from
+// beyond the L2 at 2 ns each, 28 beside a sweep), interpolation and probes 4 each, spread 4,
+// list 2; of the first, fourteen parts of 0.6 to 1.7, each a trip to memory or LDS and a barrier.
 // The particle phase after the box and its marked nodes are known; LDS: the node fields are
 // in LDS, else in the global scratch (plain loads and stores ordered by the workgroup
 // barriers, device-scope atomics for the force).
@@ -1027,26 +1035,28 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         __syncthreads();
         if (spread_ok) {
             // the compact list and its index for the sweep and the other particles' probes
-            // (PartRef; coherent stores in the phase of a single particle, whose concurrent sweep
-            // may read them, HandoverArgs), and, with no other particle's force to come, the
+            // (PartRef; coherent stores where something running beside this may read them: a
+            // single particle's sweep, HandoverArgs, and the one launch's other particles), and, with no other particle's force to come, the
             // velocities the probes read.  (A dense tile of the box instead, mostly zeros, took
             // 30 us of stores for a box of 111 x 321 nodes.)
             for (int k = tid; k < c.nmarked; k += PB) {
                 const int64_t qx = (int64_t)force_load<LDS>(B.fx + k), qy = (int64_t)force_load<LDS>(B.fy + k);
                 int64_t* t = a.tile + 2 * (size_t)k;
-                if (MODE == 0) {
+                if (MODE != 1) {
                     coherent_store(t, qx);
                     coherent_store(t + 1, qy);
+                } else {
+                    *(longlong2*)t = longlong2{(long long)qx, (long long)qy};
+                }
+                if (MODE == 0) {
                     double ux = B.ux[k], uy = B.uy[k];
                     forced_velocity(ldexp((double)qx, -scale), ldexp((double)qy, -scale), 1.0 / B.rho[k], ux, uy);
                     B.ux[k] = ux;
                     B.uy[k] = uy;
-                } else {
-                    *(longlong2*)t = longlong2{(long long)qx, (long long)qy};
                 }
             }
             for (int k = tid; k < (nbox + 31) / 32; k += PB) {
-                if (MODE == 0)
+                if (MODE != 1)
                     coherent_store((int64_t*)(a.ring + k), (int64_t)(((uint64_t)(uint32_t)pre[k] << 32) | mask[k]));
                 else
                     a.ring[k] = make_uint2(mask[k], (uint32_t)pre[k]);
@@ -1081,11 +1091,9 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             __syncthreads();  // the velocities with the spread force are complete
         }
     }
-    if (MODE == 1 || MODE == 4) {
+    if (MODE == 1) {
         __syncthreads();
         if (box_ok) mark_tiles(a, x0, y0, w, h);
-    }
-    if (MODE == 1) {
         int v[1] = {flags};
         const int op[1] = {1};
         block_int<1>(v, op, shi);
@@ -1093,9 +1101,15 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         return true;
     }
     if (MODE == 4) {
-        // every particle's list, index, box and tile bits of this step are written: meet,
-        // then read the other boxes and sum the total spread force at the marked nodes
-        if (!claimed_barrier(a.bar, a.bar_target, flags)) {
+        // every particle's list, index and box of this step are written: meet, then read the
+        // other boxes and sum the total spread force at the marked nodes.  The references (which
+        // never change) are on their way meanwhile, and the tile bits, which the sweep alone
+        // reads, are set after the meeting.
+        PartRef rq{};
+        if (tid < a.nparts) rq = a.refs[tid];
+        const bool met = claimed_barrier(a.bar, a.bar_target, flags);
+        if (box_ok) mark_tiles(a, x0, y0, w, h);
+        if (!met) {
             // a particle is unclaimed: publish this spread's flags, leave the loads to the caller
             int v[1] = {flags};
             const int op[1] = {1};
@@ -1103,12 +1117,8 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             if (tid == 0 && v[0]) atomicOr(a.flags, v[0]);
             return false;
         }
-        PartRef rq{};
         TileDesc dq{};
-        if (tid < a.nparts) {
-            rq = a.refs[tid];
-            dq = *rq.desc;
-        }
+        if (tid < a.nparts) dq = *rq.desc;
         const int nov4 = overlap_list(a, rq, dq, x0, y0, w, h, ov, shi);
         total_forces<T, LDS>(a, B, c.nodes, c.nmarked, x0, y0, w, ov, nov4);
         __syncthreads();
@@ -1405,11 +1415,14 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
 // total spread force there and evaluates the probe loads, the bonds, the wall force and the
 // rigid-body update.
 // Returns false only in MODE 4, when the phase stopped after its spread (claimed_barrier).
+// MODE 4 claims the particle first (claim_particle; took: a word of LDS) and, where another
+// workgroup has it, returns true having stored nothing.
 // shd, shi: the workgroup's reduction scratch in LDS.
 template <typename T, int MPT, int MODE>
 __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* lds, uint32_t lds_bytes,
                                                double (*shd)[NW], int (*shi)[NW], PhaseCarry* carry = nullptr,
-                                               const HelpStep& help = HelpStep{})
+                                               const HelpStep& help = HelpStep{}, int* took = nullptr,
+                                               unsigned long long launch = 0)
 {
     const int tid = threadIdx.x;
     OvEntry* ov = (OvEntry*)lds;
@@ -1439,6 +1452,8 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
             c.D.bnd[k] = a.bond[l] != 0;
         }
     }
+    // (the claim's round trip runs beside the loads above)
+    if (MODE == 4 && tid == 0) *took = claim_particle(a.bar, (int)a.pid, launch) ? 1 : 0;
     TileDesc zin{};  // the box the previous step predicted for this one (thread 0)
     if (MODE == 0 && a.check_zone && tid == 0) zin = a.zone[a.parity_in];
     c.zin = zin;
@@ -1487,6 +1502,7 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     } else {
         box_bounds<MPT>(c.G, c.D, a, shi, r);
     }
+    if (MODE == 4 && !*took) return true;  // (written before the barriers of box_bounds)
     c.nprobe = r[4];
     c.x0 = r[0];
     c.y0 = r[2];
@@ -1768,16 +1784,13 @@ __global__ __launch_bounds__(PB) void fused_particle_kernel(const ParticleArgs<T
     __shared__ int took;
     __shared__ int held[kMaxParticles];
     const int p = (int)blockIdx.x;
-    if (threadIdx.x == 0) took = claim_particle(ctr, p, launch) ? 1 : 0;
-    __syncthreads();
-    if (!took) return;
     {
         ParticleArgs<T> a = args[p];
         a.f = f;
         a.pmask = pmask;
         a.bar = ctr;
         a.bar_target = target;
-        if (particle_phase<T, MPT, 4>(a, (char*)lds_dyn, lds_bytes, shd, shi)) return;
+        if (particle_phase<T, MPT, 4>(a, (char*)lds_dyn, lds_bytes, shd, shi, nullptr, HelpStep{}, &took, launch)) return;
     }
     int nheld = 0;
     for (int q = 0; q < np; ++q) {

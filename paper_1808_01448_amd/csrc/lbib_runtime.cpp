@@ -410,7 +410,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
             pa.zone_tag = (uint32_t)((prev + 1) & 0xffffu);
             h->plaunches = prev + 1;
             // the overlapped schedule is the faster one at every size measured, from 256 x 64
-            // (20.1 against 21.9 us per step: the sweep hides behind the particle phase) to
+            // (15.0 against 19.4 us per step: the sweep hides behind the particle phase) to
             // 8192 x 4096 (the particle phase hides behind the sweep).  It needs the CU-masked
             // sweep stream: workgroups of the sweep and the particle's wait for each other on
             // the device, and the particle must always find a CU.
