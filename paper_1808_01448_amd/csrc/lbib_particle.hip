@@ -1343,32 +1343,6 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
     return true;
 }
 
-// The overlapped schedule (thread 0, before the barrier that precedes the fill): the previous
-// sweep's zone workgroups have stored this step's populations around the box (coherently) once
-// they have all counted in; the acquire drops stale copies from this CU's caches before any of
-// them is read.  Nothing before the fill reads a population, so the marks and the map of the
-// nodes are formed while those workgroups still run.
-template <typename T, int MPT>
-__device__ __forceinline__ void zone_wait(const ParticleArgs<T>& a, PhaseCtx<MPT>& c)
-{
-    if (!c.helped) {
-        wait_counter(a.zdone, a.zdone_target, a.flags);
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    if (a.check_prev && c.box_ok) {
-        // those workgroups covered the previous box (of the last two steps swept together,
-        // the first's) widened by kZoneMargin: this box must lie in it widened by
-        // kZoneMargin - 1 (its readers' sources one further)
-        const TileDesc zp = a.zone[a.check_prev == 2 ? 2 : a.parity_out];
-        const int m = kZoneMargin - 1;
-        int dx = ((c.x0 - zp.i0w) % a.nx + a.nx) % a.nx;
-        if (dx >= a.nx / 2) dx -= a.nx;
-        const bool okx = zp.w + 2 * m >= a.nx || (dx >= -m && dx + c.w <= zp.w + m);
-        const bool oky = c.y0 >= zp.j0 - m && c.y0 + c.h <= zp.j0 + zp.h + m;
-        if (!zp.active || !okx || !oky) c.flags |= FLAG_TILE;
-    }
-}
-
 // Lays out the node fields and the node map of the marked nodes from base (LDS: dynamic LDS,
 // else the global scratch), writes the map and runs the rest of the phase.
 template <typename T, int MPT, bool LDS, int MODE>
@@ -1395,7 +1369,15 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     } else {
         write_node_map<stride>(c.mask, c.pre, (c.nbox + 31) / 32, nodes);
     }
-    if (MODE == 0 && a.zdone && threadIdx.x == 0) zone_wait(a, c);
+    if (MODE == 0 && a.zdone && threadIdx.x == 0 && !c.helped) {
+        // the overlapped schedule: the previous sweep's zone workgroups have stored this step's
+        // populations around the box (coherently) once they have all counted in; the acquire
+        // drops stale copies from this CU's caches before any of them is read.  Nothing before
+        // the fill reads a population, so the marks and the map of the nodes are formed while
+        // those workgroups still run.
+        wait_counter(a.zdone, a.zdone_target, a.flags);
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
     if (can_help && c.carry && c.help.use && c.help.me == 0 && threadIdx.x < 64)
         help_wait(c.help.area, c.help.base + (unsigned long long)(c.help.next - 1), a.flags);
     __syncthreads();
@@ -1510,6 +1492,19 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     c.h = (r[2] != 0x7fffffff) ? -r[3] - r[2] + 1 : 0;
     c.box_ok = c.w > 0 && c.h > 0 && c.w <= a.nx && (int64_t)c.w * c.h <= a.box_cap;
     if (!c.box_ok && tid == 0) c.flags |= FLAG_TILE;
+    if (MODE == 0 && a.zdone && a.check_prev && c.box_ok && tid == 0) {
+        // the previous sweep's zone workgroups covered the previous box (of the last two steps
+        // swept together, the first's) widened by kZoneMargin: this box must lie in it widened
+        // by kZoneMargin - 1 (its readers' sources one further)
+        const TileDesc zp = a.zone[a.check_prev == 2 ? 2 : a.parity_out];
+        const int m = kZoneMargin - 1;
+        int dx = ((c.x0 - zp.i0w) % a.nx + a.nx) % a.nx;
+        if (dx >= a.nx / 2) dx -= a.nx;
+        const bool okx = zp.w + 2 * m >= a.nx || (dx >= -m && dx + c.w <= zp.w + m);
+        const bool oky = c.y0 >= zp.j0 - m && c.y0 + c.h <= zp.j0 + zp.h + m;
+        if (!zp.active || !okx || !oky) c.flags |= FLAG_TILE;
+    }
+
     // ---- the nodes this launch's supports reach, and their slots ------------------------
     c.nbox = c.box_ok ? c.w * c.h : 0;
     const int nw = (c.nbox + 31) / 32;
