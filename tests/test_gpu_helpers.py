@@ -45,3 +45,31 @@ def test_same_as_serial(which, precision, layout):
             res.append((s.trace(sum(calls)), s.bonds()[0], s.f))
     for a, b in zip(*res):
         assert np.array_equal(np.asarray(a), np.asarray(b))
+
+
+def test_several_at_once():
+    """Three simulations with helpers, their calls enqueued in turn with no wait between them."""
+    from paper_1808_01448_amd import lbib
+
+    ws = []
+    for k in range(3):
+        w = W.channel_small_fp64()
+        w["lattice"].update(nx=600 + 37 * k, ny=300, re=1.0, precision=W.PRECISION["bf16_neq"], seed=k)
+        w["particle"].update(SHAPES["two_a_thread"], xc=250.5, yc=98.0 + 0.5 * W.Y_CR_HAT * 300 - 0.5, theta0=0.0)
+        ws.append(w)
+
+    def final(overlap):
+        sims = [lbib.Sim(w) for w in ws]
+        for s in sims:
+            s.set_overlap(overlap)
+        for n in (40, 25, 60):
+            for s in sims:
+                s.step(n)
+        out = []
+        for s in sims:
+            s.sync()
+            out.append((s.particle(), s.bonds()[0].tobytes(), s.f.tobytes()))
+            s.close()
+        return out
+
+    assert final(2) == final(0)
