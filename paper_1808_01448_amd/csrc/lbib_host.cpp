@@ -206,21 +206,46 @@ int pair_zone_workgroups(const Particle& p, int rows)
     return std::min(64, (cols * units * ((rows + 3) / 4) + 7) / 8 * 8);
 }
 
+// Whether the two-step sweeps can address the buffers: they reach all nine populations of three
+// rows through one 32-bit window of three pitches (row_window), which holds them only where a
+// row's nine segments are adjacent (in population planes, rows of more than 2^31 / 9 nodes, a
+// window that short has one population).  Not the f - f_eq storages: their sweep is not bound by
+// traffic.
+static bool pair_window(const LatticeGeom& g)
+{
+    return !g.neq && g.interleaved && 3 * (int64_t)g.pitch * (int64_t)g.elem < (int64_t)1 << 31;
+}
+
 // Whether a simulation's sweeps take two steps in one pass over memory (PairHandover): from
-// kPairBytes of traffic per step, and where a window of three rows fits a buffer resource's
-// bound.  us per step, one step per sweep -> two, with a particle / without: 2.4 MB (256 x 64
+// kPairBytes of traffic per step.  us per step, one step per sweep -> two, with a particle / without: 2.4 MB (256 x 64
 // FP64) 17.3 -> 17.3 / 2.9 -> 2.9 and calls of 6 steps 22.3 -> 22.9 / 4.8 -> 4.9; 9.4 MB 19.0 ->
 // 18.5 / 3.3 -> 3.1, 6-step calls 23.9 -> 24.3; 19 MB (1024 x 256 FP32) 20.9 -> 19.2 / 4.5 ->
 // 4.4; 58 MB (2000 x 200 FP64) 21.7 -> 19.7 / 9.9 -> 6.1; 302 MB (4096 x 1024 FP32) 44.2 -> 35.3 /
 // 42.9 -> 32.7; 2.4 GB 399 -> 280; FP64 604 MB 95 -> 75 (a 960-marker particle), FP16 1.2 GB 204 ->
-// 154.  Below, short calls lose as much as long ones gain.  Not the f - f_eq storages: their
-// sweep is not bound by traffic.
+// 154.  Below, short calls lose as much as long ones gain.
 bool pair_sweeps(const LatticeGeom& g)
 {
     constexpr double kPairBytes = 16e6;
-    return !g.neq && 3 * (int64_t)g.pitch * (int64_t)g.elem < (int64_t)1 << 31 &&
-           (double)g.upd_bytes * g.nx * g.ny >= kPairBytes;
+    return pair_window(g) && (double)g.upd_bytes * g.nx * g.ny >= kPairBytes;
 }
+
+// Whether a pool's do: from kPairBytes of traffic per step.  The pass saves most of every second
+// step's traffic, and costs the zone launch, a wave's march over its rows in turn and two extra
+// rows per run, which smaller pools do not get back (us per step, one step per sweep against two,
+// with the particle launches: 59 MB FP32 37.0 against 39.8, 75 MB 37.5 / 39.2, 118 MB 49.3 / 41.9,
+// 302 MB 84 / 65, 944 MB 210 / 138; FP64 118 MB 48.8 / 45.3, FP16 75 MB 39.2 / 42.9, 118 MB 47.5 /
+// 44.6).
+bool pool_pair_sweeps(const std::vector<LatticeGeom>& members)
+{
+    constexpr double kPairBytes = 100e6;
+    double bytes = 0.0;
+    for (const LatticeGeom& g : members) {
+        if (!pair_window(g)) return false;
+        bytes += (double)g.upd_bytes * g.nx * g.ny;
+    }
+    return bytes >= kPairBytes;
+}
+
 // Rows of a unit.  Alone, enough units to fill the GPU: a wave's rows go one after the other (4
 // rows 6.1, 8 6.0, 16 7.7 us per step on 2000 x 200 FP64; 1500 x 384 FP32 6.1, 6.8, 7.5; 4096 x
 // 1024 FP32 8 rows 32.7, 16 33.8; beyond 2^23 nodes 16 rows 276, 8 288).  Beside a particle the

@@ -128,6 +128,7 @@ inline size_t align_up(size_t n) { return (n + kAlign - 1) / kAlign * kAlign; }
 int zone_workgroups(const Particle& p, bool pull);
 int pair_zone_workgroups(const Particle& p, int rows);
 bool pair_sweeps(const LatticeGeom& g);
+bool pool_pair_sweeps(const std::vector<LatticeGeom>& members);
 int pair_rows(const LatticeGeom& g, bool particle);  // rows of a unit of the two-step sweep
 size_t particle_block_bytes(const Particle& p);
 // Point the particle's buffers into `block` (particle_block_bytes(p) bytes, not owned).

@@ -101,7 +101,8 @@ struct BoxForce {
 // q) is the scalar offset dr R + q P, a column the lane's offset.  The loop then issues every
 // access without a branch around it (a lane that has nothing to store gives kNoStore, which the
 // resource's bound drops), so the compiler knows how many younger accesses are in flight when
-// it waits for a row's loads and does not wait for those.
+// it waits for a row's loads and does not wait for those.  Row-interleaved buffers only (R = 9 P):
+// the window's three pitches then hold all nine populations of its three rows.
 constexpr uint32_t kNoStore = 0xC0000000u;  // beyond every bound (the window's bytes are below 2^31)
 
 template <typename S>

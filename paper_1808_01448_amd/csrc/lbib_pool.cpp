@@ -207,26 +207,6 @@ void ensure(T*& d, size_t& cap, size_t need, hipError_t& e)
     if (e == hipSuccess) cap = c;
 }
 
-// Whether the pool's sweeps take two steps in one pass over memory: from kPairBytes of traffic
-// per step.  The pass saves most of every second step's traffic, and costs the zone launch, a
-// wave's march over its rows in turn and two extra rows per run, which smaller pools do not get
-// back (us per step, one step per sweep against two, with the particle launches: 59 MB FP32 37.0
-// against 39.8, 75 MB 37.5 / 39.2, 118 MB 49.3 / 41.9, 302 MB 84 / 65, 944 MB 210 / 138; FP64
-// 118 MB 48.8 / 45.3, FP16 75 MB 39.2 / 42.9, 118 MB 47.5 / 44.6).  The f - f_eq storages keep
-// one step (their sweep is not bound by traffic), as do rows whose window exceeds a buffer
-// resource's bound.
-constexpr double kPairBytes = 100e6;
-template <typename T>
-bool pair_sweeps(const std::vector<Member*>& run)
-{
-    double bytes = 0.0;
-    for (const Member* m : run) {
-        if (3 * (int64_t)m->g.pitch * (int64_t)sizeof(typename St<T>::raw) >= (int64_t)1 << 31) return false;
-        bytes += (double)m->g.upd_bytes * m->g.nx * m->g.ny;
-    }
-    return !St<T>::neq && bytes >= kPairBytes;
-}
-
 // Rebuild the launch tables from the running members (the stream is idle when called).
 // Members with the most markers come first so the longest particle phases start first.
 template <typename T>
@@ -240,6 +220,7 @@ lbib_status rebuild(lbib_pool* h)
     std::vector<int32_t> active(run.size());
     std::vector<PoolSweep<T>> sims(run.size());
     std::vector<int2> table, ptable;
+    std::vector<LatticeGeom> geoms;
     std::vector<size_t> tile_off(run.size());
     size_t tile_elems = 0;
     const int prows = pool_pair_rows(h->cfg);
@@ -272,6 +253,7 @@ lbib_status rebuild(lbib_pool* h)
         if ((int64_t)table.size() + s.ntiles / h->cfg.tpb + 1 > 0x7fffffff)
             return fail(h, LBIB_E_INVALID, "pool: more than 2^31 sweep blocks");
         for (int32_t t = 0; t < s.ntiles; t += h->cfg.tpb) table.push_back(make_int2((int)k, t));
+        geoms.push_back(m.g);
         s.zone = m.p.d_zone;
         tile_off[k] = tile_elems;
         tile_elems += 2 * (size_t)m.p.box_cap + (size_t)(m.p.box_cap + 31) / 32;  // the list, then its index
@@ -281,7 +263,7 @@ lbib_status rebuild(lbib_pool* h)
         for (int32_t t = 0; t < px * py; ++t) ptable.push_back(make_int2((int)k, t));
     }
     hipError_t e = hipSuccess;
-    h->pairs = pair_sweeps<T>(run);
+    h->pairs = pool_pair_sweeps(geoms);
     if (h->pairs) {
         ensure(h->d_ptable, h->ptable_cap, ptable.size(), e);
         ensure(h->d_tile_b, h->tile_b_cap, tile_elems, e);

@@ -285,6 +285,7 @@ hipError_t launch_sweep_pair(const T* fin, T* fout, const SweepArgs& a, const Pa
                              hipStream_t stream, hipEvent_t t0, hipEvent_t t1, bool rev)
 {
     if (c.h.nzone < 0 || c.h.nzone > 64 || c.h.nzone % 8 || rows < 1) return hipErrorInvalidValue;
+    if (a.pitch != 9 * a.plane) return hipErrorInvalidValue;  // rows of nine segments (row_window)
     if constexpr (St<T>::neq) {
         return hipErrorInvalidValue;
     } else {

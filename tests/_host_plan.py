@@ -1,0 +1,67 @@
+"""The host-side rules of the library, called through a small C++ shim linked with it (no GPU is
+used): the shim is compiled here against the library's internal headers."""
+import ctypes as C
+import functools
+import os
+import subprocess
+import tempfile
+
+from paper_1808_01448_amd import build, lbib
+
+SHIM = r"""
+#include "lbib_host.hpp"
+using namespace lbib;
+extern "C" {
+// interleaved, pitch, plane, element bytes, one simulation's two-step sweeps, their rows per unit
+// alone and beside a particle
+void plan_lattice(const lbib_lattice_desc* d, int64_t* out)
+{
+    const LatticeGeom g = lattice_geom(*d);
+    out[0] = g.interleaved;
+    out[1] = g.pitch;
+    out[2] = g.plane;
+    out[3] = (int64_t)g.elem;
+    out[4] = pair_sweeps(g);
+    out[5] = pair_rows(g, false);
+    out[6] = pair_rows(g, true);
+}
+int plan_pool(const lbib_lattice_desc* d, int64_t n)
+{
+    std::vector<LatticeGeom> g;
+    for (int64_t k = 0; k < n; ++k) g.push_back(lattice_geom(d[k]));
+    return pool_pair_sweeps(g);
+}
+}
+"""
+
+
+@functools.lru_cache(maxsize=1)
+def shim():
+    if not os.path.exists(lbib.LIB_PATH):
+        build.build()
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "shim.cpp"), os.path.join(d, "shim.so")
+        with open(src, "w") as f:
+            f.write(SHIM)
+        libdir = os.path.dirname(lbib.LIB_PATH)
+        subprocess.check_call([build.hipcc(), *build.FLAGS, "-w", "-shared", src, "-o", so, "-L", libdir,
+                               "-l:" + os.path.basename(lbib.LIB_PATH), f"-Wl,-rpath,{libdir}"])
+        return C.CDLL(so)
+
+
+def lattice_desc(nx, ny, precision, drive=0):
+    from paper_1808_01448_amd import workloads as W
+
+    return lbib.LatticeDesc(nx, ny, 0.8, 0.5, drive, W.PRECISION[precision], 0)
+
+
+def lattice(nx, ny, precision):
+    out = (C.c_int64 * 7)()
+    shim().plan_lattice(C.byref(lattice_desc(nx, ny, precision)), out)
+    return dict(zip(("interleaved", "pitch", "plane", "elem", "pairs", "rows_alone", "rows_particle"), out))
+
+
+def pool_pairs(members):
+    """members: (nx, ny, precision) each."""
+    d = (lbib.LatticeDesc * len(members))(*[lattice_desc(*m) for m in members])
+    return bool(shim().plan_pool(d, C.c_int64(len(members))))

@@ -1,0 +1,49 @@
+"""The rules that choose a sweep, evaluated on the host.  CPU only."""
+import itertools
+
+import pytest
+
+import _host_plan as H
+
+INT32_MAX = 2**31 - 1
+ELEM = {"fp64": 8, "fp32": 4, "fp16": 2, "bf16": 2}
+
+
+def columns(prec):
+    """Around the row length at which lattice_geom turns from rows of nine segments to population
+    planes, and around those whose window reaches a buffer resource's bound."""
+    align = 256 // ELEM[prec]
+    edge = INT32_MAX // 9 // align * align
+    bound = {"rows": 2**31 // (27 * ELEM[prec]), "planes": 2**31 // (3 * ELEM[prec])}
+    near = [edge + d for d in (-align, 0, 1, align, 2 * align)]
+    near += [b // align * align + d for b in bound.values() for d in (-align, 0, 1, align)]
+    return sorted({n for n in near + [4, 61, 4096, 8192, 300_000_000, 357_000_000] if n * 4 <= 2**31})
+
+
+@pytest.mark.parametrize("prec", list(ELEM))
+def test_two_step_windows_hold_every_population(prec):
+    """Where one simulation or a pool sweeps two steps in one pass, the window of three pitches
+    that starts a row below a node's holds all nine populations of the three rows, and its
+    offsets fit 32 bits."""
+    chosen = 0
+    for nx, ny in itertools.product(columns(prec), (4, 7, 9)):
+        if nx * ny > 2**31:
+            continue
+        g = H.lattice(nx, ny, prec)
+        if not (g["pairs"] or H.pool_pairs([(nx, ny, prec)])):
+            continue
+        chosen += 1
+        window = 3 * g["pitch"] * g["elem"]
+        # the last access: row 2 of the window, population 8, the last column
+        last = (2 * g["pitch"] + 8 * g["plane"] + nx) * g["elem"]
+        assert last <= window < 2**31, (nx, ny, g)
+    assert chosen > 0
+
+
+@pytest.mark.parametrize("prec", ["fp16", "bf16"])
+def test_population_planes_are_swept_step_by_step(prec):
+    """238 609 408 columns: nine rows exceed a 32-bit pitch, three planes' rows do not."""
+    g = H.lattice(238_609_408, 4, prec)
+    assert not g["interleaved"] and 3 * g["pitch"] * g["elem"] < 2**31
+    assert not g["pairs"]
+    assert not H.pool_pairs([(2048, 4096, prec), (238_609_408, 4, prec)])
