@@ -257,6 +257,54 @@ int pair_rows(const LatticeGeom& g, bool particle)
     return particle || nodes >= (int64_t)1 << 23 ? 16 : nodes >= (int64_t)1 << 20 ? 8 : 4;
 }
 
+MarkedNodes marked_nodes(const Particle& p, int ny, double xc, double yc, double th)
+{
+    struct Window {
+        int64_t ilo, ihi, jlo, jhi;
+    };
+    auto row = [&](double y) { return std::min(std::max(y, 0.0), ny - 1.0); };
+    const double c = std::cos(th), s = std::sin(th);
+    std::vector<Window> ws;
+    int64_t x0 = INT64_MAX, x1 = INT64_MIN, y0 = INT64_MAX, y1 = INT64_MIN;
+    auto add = [&](double X, double Y) {
+        const Window w{(int64_t)std::floor(X - 1.5) + 1, (int64_t)std::ceil(X + 1.5) - 1,
+                       std::max<int64_t>((int64_t)std::floor(Y - 1.5) + 1, 0),
+                       std::min<int64_t>((int64_t)std::ceil(Y + 1.5) - 1, ny - 1)};
+        if (w.jhi < w.jlo) return;
+        x0 = std::min(x0, w.ilo);
+        x1 = std::max(x1, w.ihi);
+        y0 = std::min(y0, w.jlo);
+        y1 = std::max(y1, w.jhi);
+        ws.push_back(w);
+    };
+    for (int l = 0; l < p.nl; ++l) {
+        const double bx = p.surf.xi[2 * l], by = p.surf.xi[2 * l + 1], mx = p.surf.nu[2 * l], my = p.surf.nu[2 * l + 1];
+        const double X = xc + c * bx - s * by, Y = yc + s * bx + c * by;
+        add(X, row(Y));
+        add(X + 1.2 * (c * mx - s * my), row(Y + 1.2 * (s * mx + c * my)));
+    }
+    if (ws.empty()) return MarkedNodes{0, 0};
+    const int64_t w = x1 - x0 + 1;
+    std::vector<bool> mark((size_t)(w * (y1 - y0 + 1)));
+    for (const Window& k : ws)
+        for (int64_t j = k.jlo; j <= k.jhi; ++j)
+            for (int64_t i = k.ilo; i <= k.ihi; ++i) mark[(size_t)((j - y0) * w + (i - x0))] = true;
+    return MarkedNodes{(int64_t)std::count(mark.begin(), mark.end(), true), (int64_t)mark.size()};
+}
+
+// Whether a simulation's resident particle launch gets helpers (HelpArea): the f - f_eq storages,
+// from kHelpMarkers markers, where at the particle's first pose the fields of its nodes fit in
+// LDS (us per step of 1024 markers as f - f_eq, a launch per step against the resident one: 244 x
+// 240, 3614 nodes of the 3665 that fit, 57.6 -> 50.3 with helpers; 252 x 248, 3723 of 3640, 83.5
+// -> 81.2 without).  A particle that outgrows LDS as it turns keeps its helpers, which then wait
+// for a step that fits.
+bool with_helpers(const LatticeGeom& g, const Particle& p)
+{
+    if (!g.neq || p.nl < kHelpMarkers) return false;
+    const MarkedNodes m = marked_nodes(p, g.ny, p.desc.xc, p.desc.yc, p.desc.theta0);
+    return m.nodes <= kHelpNodes && m.box <= p.box_cap && m.nodes <= particle_lds_slots(p.box_cap, (int32_t)m.box);
+}
+
 size_t particle_block_bytes(const Particle& p)
 {
     const size_t nl = (size_t)p.nl, cap = (size_t)p.box_cap;

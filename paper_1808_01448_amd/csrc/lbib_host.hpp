@@ -130,6 +130,13 @@ int pair_zone_workgroups(const Particle& p, int rows);
 bool pair_sweeps(const LatticeGeom& g);
 bool pool_pair_sweeps(const std::vector<LatticeGeom>& members);
 int pair_rows(const LatticeGeom& g, bool particle);  // rows of a unit of the two-step sweep
+// The nodes that the supports of the particle's markers and probes reach at a pose, and the nodes
+// of the box that holds them.
+struct MarkedNodes {
+    int64_t nodes, box;
+};
+MarkedNodes marked_nodes(const Particle& p, int ny, double xc, double yc, double th);
+bool with_helpers(const LatticeGeom& g, const Particle& p);
 size_t particle_block_bytes(const Particle& p);
 // Point the particle's buffers into `block` (particle_block_bytes(p) bytes, not owned).
 void carve_particle(Particle& p, char* block);

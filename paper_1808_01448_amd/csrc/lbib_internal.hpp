@@ -314,6 +314,8 @@ size_t particle_lds_bytes(int32_t box_cap);
 size_t particle_lds_aux_bytes(int32_t box_cap);
 size_t particle_launch_lds(int32_t box_cap);
 size_t particle_scratch_bytes(int32_t box_cap);
+// Marked nodes of a box of nbox nodes whose fields that launch holds in LDS.
+int32_t particle_lds_slots(int32_t box_cap, int32_t nbox);
 template <typename T>
 hipError_t launch_particle(const ParticleArgs<T>& a, hipStream_t stream, hipEvent_t t0 = nullptr,
                            hipEvent_t t1 = nullptr);
@@ -330,7 +332,7 @@ hipError_t launch_particle(const ParticleArgs<T>& a, hipStream_t stream, hipEven
 // help (or NULL; the f - f_eq storages): the run is launched with kHelpers more workgroups, which
 // fill the node fields of its steps (HelpArea).
 constexpr int kHelpers = 8;
-constexpr int kHelpMarkers = 384;  // the particle that has them (lbib_particle.hip: HelpStep)
+constexpr int kHelpMarkers = 384;  // the particle that has them (with_helpers)
 constexpr int kHelpNodes = 4096;  // as many as LDS can hold node fields of
 struct HelpArea {
     unsigned long long msg[8];      // the pose a step starts from: six tagged half words

@@ -185,10 +185,16 @@ constexpr int kFields = 5;                      // per marked node: 3 doubles + 
 constexpr size_t kSlotBytes = kFields * 8 + 4;  // the fields and the node map entry
 constexpr size_t kScratchSlot = 52;             // global scratch of a box node
 constexpr int map_stride(int mode) { return mode == 4 ? 1 : 2; }  // of the node map, in words (phase_rest)
-constexpr size_t slot_bytes(int mode) { return mode == 4 ? kSlotBytes : kSlotBytes - 4; }
+__host__ __device__ constexpr size_t slot_bytes(int mode) { return mode == 4 ? kSlotBytes : kSlotBytes - 4; }
 constexpr int kFillU = 4;                       // marked nodes per lane in flight while summing forces
 constexpr size_t kLdsMax = 158 * 1024;          // dynamic LDS a workgroup may take beside the static part
 constexpr size_t kLdsHead = sizeof(OvEntry) * kMaxParticles;
+// Marked nodes whose fields fit in the launch's LDS beside the mask and its prefix counts (aux
+// bytes).
+__host__ __device__ constexpr int lds_slots(size_t lds_bytes, size_t aux, int mode)
+{
+    return lds_bytes > aux ? (int)((lds_bytes - aux) / slot_bytes(mode)) : 0;
+}
 
 size_t particle_lds_aux_bytes(int32_t box_cap)
 {
@@ -209,6 +215,11 @@ size_t particle_launch_lds(int32_t box_cap)
 size_t particle_scratch_bytes(int32_t box_cap)
 {
     return particle_lds_bytes(box_cap) ? 0 : (size_t)box_cap * kScratchSlot;
+}
+
+int32_t particle_lds_slots(int32_t box_cap, int32_t nbox)
+{
+    return lds_slots(particle_launch_lds(box_cap), (size_t)((nbox + 31) / 32) * 8, 0);
 }
 
 // The markers of this thread (l = threadIdx.x + k PB) at one position of the particle.
@@ -754,7 +765,12 @@ struct PhaseCarry {
 // in; the leader reads three values per node, in slot order.
 //   The leader never depends on a helper that has not started: it fills its nodes itself until
 // all have (arrived), so a helper that finds no room beside other work costs speed alone.  It
-// sends a pose only once every helper has counted in for the previous one, so none is missed.
+// waits for every helper's count before it goes on with a shared step, so none misses one.
+//   A step whose nodes LDS does not hold is the leader's alone (its fields then lie in a scratch
+// that plain stores of workgroups on several XCDs must not meet in): a helper that has its pose
+// stores nothing but its count, which nobody waits for, and the leader sends no pose after it,
+// until a step fits again.  A particle whose nodes do not fit at its first pose has no helpers
+// (with_helpers).
 //   us per step alone -> helped, stored as f - f_eq: 384 markers (512 x 400) 31.6 -> 30.1, 576
 // (2048 x 600) 48.1 -> 40.5, 640 (2999 x 777) 62.8 -> 50.5, 832 (2048 x 900) 67.1 -> 47.8.  The
 // hand-over costs about as much as the whole fill of the other storages (832 markers FP32 40.2 ->
@@ -773,9 +789,10 @@ __device__ __forceinline__ uint32_t help_tag(const HelpStep& s, int32_t k, bool 
 {
     return ((uint32_t)(s.base + (unsigned long long)k) << 1) | (use ? 1u : 0u);
 }
-// The leader's thread 0, with the pose of step s.next.  The words carry their tag, so they need
-// no order and no flag.  The pose after the run's last step, which nobody fills, ends the helpers.
-__device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, double x, double yy, double th)
+// The leader's thread 0, with the pose of step s.next, for the helpers where this step's fields
+// were shared (fits).  The words carry their tag, so they need no order and no flag.  The pose
+// after the run's last step, which nobody fills, ends the helpers.
+__device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, bool fits, double x, double yy, double th)
 {
     if (!y.present) {
         bool all = true;
@@ -784,7 +801,7 @@ __device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, doub
             all &= (unsigned long long)coherent_load((const int64_t*)s.area->arrived + k) == s.base;
         y.present = all;
     }
-    const bool use = y.present && s.next < s.nsteps;
+    const bool use = y.present && fits && s.next < s.nsteps;
     y.use = use;
     if (!use && s.next < s.nsteps) return;
     const unsigned long long tag = (unsigned long long)help_tag(s, s.next, use) << 32;
@@ -910,7 +927,8 @@ struct PhaseCtx {
     TileDesc zin;
     PhaseCarry* carry;
     HelpStep help;
-    bool helped;  // (the leader) this step's node fields come from the helpers
+    bool shared;  // the step's node fields can come from helpers: they lie in LDS and fit HelpArea
+    bool helped;  // (the leader) and do
 };
 
 // The phase runs on one CU, so it is bound by the latency of its chain for small particles and
@@ -1243,7 +1261,8 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         const double nth = (2.0 / 3.0) * (2.0 * th - 0.5 * c.th1 + nom);
         if (!(isfinite(Fx) && isfinite(Fy) && isfinite(M) && isfinite(nux) && isfinite(nuy) && isfinite(nom)))
             fl |= FLAG_NONFINITE;
-        if (kHelped<T> && MODE == 0 && c.carry && c.help.area) help_send(c.help, *c.carry, nxc, nyc, nth);
+        if (kHelped<T> && MODE == 0 && c.carry && c.help.area)
+            help_send(c.help, *c.carry, c.shared, nxc, nyc, nth);
         // the state the next step starts from, stored coherently (as the bond flags)
         state_store(&st->xc1, xc);
         state_store(&st->yc1, yc);
@@ -1361,8 +1380,10 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     int* nodes = stride == 2 ? (int*)B.fx : (int*)(base + 5 * m);
     c.nodes = nodes;
     constexpr bool can_help = kHelped<T> && MODE == 0;  // (and a resident launch's: carry)
-    const bool share = LDS && m <= kHelpNodes;  // the leader's and the helpers' verdicts agree
-    c.helped = can_help && c.carry && c.help.use && c.help.me == 0 && share;
+    c.shared = LDS && m <= kHelpNodes;  // the leader's and the helpers' verdicts agree
+    // a helper of a step that is not shared is done: the global scratch is the leader's alone
+    if (can_help && c.carry && c.help.me != 0 && !c.shared) return true;
+    c.helped = can_help && c.carry && c.help.use && c.help.me == 0 && c.shared;
     if (c.helped) {
     } else if (c.whole) {
         if ((int)threadIdx.x < m) nodes[(int)threadIdx.x * stride] = (int)threadIdx.x;
@@ -1378,11 +1399,11 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
         wait_counter(a.zdone, a.zdone_target, a.flags);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    if (can_help && c.carry && c.help.use && c.help.me == 0 && threadIdx.x < 64)
+    if (c.helped && threadIdx.x < 64)
         help_wait(c.help.area, c.help.base + (unsigned long long)(c.help.next - 1), a.flags);
     __syncthreads();
     if (can_help && c.carry && c.help.me != 0) {
-        if (share) help_fill(a, c.help, nodes, stride, m, c.x0, c.y0, c.w);
+        help_fill(a, c.help, nodes, stride, m, c.x0, c.y0, c.w);
         return true;
     }
     return phase_body<T, MPT, LDS, MODE>(a, c, B, ov, nov, shd, shi);
@@ -1511,7 +1532,6 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     int* pre = (int*)(mask + nw);
     double* fields = (double*)(pre + nw);  // 8-byte aligned: head and 8 nw are multiples of 8
     const size_t aux = head + (size_t)nw * 8;
-    const int lds_slots = lds_bytes > aux ? (int)((lds_bytes - aux) / slot_bytes(MODE)) : 0;
     // A box of at most a node per thread is taken whole: every node of it costs the fill no more
     // than the marked ones, and the marks, their prefix and the map are not needed (2.2 us of 16
     // for a box of 16 x 14 nodes).  A node that no support reaches gets a zero force.
@@ -1536,7 +1556,7 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     const int nov = MODE == 2 ? overlap_list(a, rq, dq, c.x0, c.y0, c.w, c.h, ov, shi) : 0;
 
     // fields and node map in LDS when they fit, else in the global scratch
-    const bool fits = c.nmarked <= lds_slots;
+    const bool fits = c.nmarked <= lds_slots(lds_bytes, aux, MODE);
     if (!fits && !a.box_global) {  // no scratch to hold them (a launch with too little LDS)
         c.box_ok = false;
         c.nbox = 0;

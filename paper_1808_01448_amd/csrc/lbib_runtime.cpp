@@ -762,7 +762,7 @@ lbib_status lbib_init(lbib_handle h)
             h->pairs = false;
         }
     }
-    if (h->parts.size() == 1 && h->parts[0].nl >= kHelpMarkers && h->g.neq) {
+    if (h->parts.size() == 1 && with_helpers(h->g, h->parts[0])) {
         e = hipMalloc((void**)&h->d_help, sizeof(HelpArea));
         if (e == hipSuccess) {
             if ((e = hipMemsetAsync(h->d_help, 0, sizeof(HelpArea), h->stream)) != hipSuccess)

@@ -25,6 +25,19 @@ void plan_lattice(const lbib_lattice_desc* d, int64_t* out)
     out[5] = pair_rows(g, false);
     out[6] = pair_rows(g, true);
 }
+// helpers, marked nodes at a pose (NULL: the first) and those that LDS holds there; -1: refused
+int plan_particle(const lbib_lattice_desc* d, const lbib_particle_desc* pd, const double* pose, int64_t* out)
+{
+    Particle p;
+    std::string msg;
+    if (prepare_particle(*d, *pd, p, msg) != LBIB_OK) return -1;
+    const MarkedNodes m = pose ? marked_nodes(p, d->ny, pose[0], pose[1], pose[2])
+                               : marked_nodes(p, d->ny, pd->xc, pd->yc, pd->theta0);
+    out[0] = with_helpers(lattice_geom(*d), p);
+    out[1] = m.nodes;
+    out[2] = particle_lds_slots(p.box_cap, (int32_t)m.box);
+    return 0;
+}
 int plan_pool(const lbib_lattice_desc* d, int64_t n)
 {
     std::vector<LatticeGeom> g;
@@ -65,3 +78,15 @@ def pool_pairs(members):
     """members: (nx, ny, precision) each."""
     d = (lbib.LatticeDesc * len(members))(*[lattice_desc(*m) for m in members])
     return bool(shim().plan_pool(d, C.c_int64(len(members))))
+
+
+def particle(w, pose=None):
+    """Of a workload's particle: helpers, and at the pose (x, y, theta; None: its first) the marked
+    nodes and how many LDS holds."""
+    lat, p = w["lattice"], w["particle"]
+    d = lbib.LatticeDesc(lat["nx"], lat["ny"], lat["tau"], lat["re"], lat.get("drive", 0), lat["precision"], 0)
+    pd = lbib.ParticleDesc(*[p[k] for k, _ in lbib.ParticleDesc._fields_])
+    out = (C.c_int64 * 3)()
+    at = None if pose is None else (C.c_double * 3)(*pose)
+    assert shim().plan_particle(C.byref(d), C.byref(pd), at, out) == 0
+    return dict(helpers=bool(out[0]), nodes=out[1], slots=out[2])
