@@ -233,13 +233,15 @@ lbib_status lbib_load(lbib_handle h, const void* blob, int64_t size);
  * second stream the handle owns and the lattice sweeps on a third (CU-masked: one CU is left
  * to the particle), with no event between the two chains; they hand over through device
  * memory.  The sweep of step n reads the box step n-1 predicted (exactly) for step n and
- * leaves the node tiles of that box, widened by 3 nodes, to workgroups at the head of its
- * grid, which take them once particle phase n has published its spread force; particle phase
- * n+1 starts once those workgroups have stored step n+1's populations around its box.  Every
- * device-side wait is bounded: one that exceeds about a second fails the simulation with
- * LBIB_E_NUMERIC.  Its two streams must run concurrently: a tool that serialises kernel
- * dispatches (hardware-counter collection) makes those waits time out, so run mode 0 under it.  Serial (mode 0), always on the first step after lbib_init / lbib_load /
- * lbib_write_particle, and where CU masking is unavailable or ny >= 2^23: the particle phase
+ * leaves the node tiles of that box, widened by 3 nodes (5 where a sweep may take two steps,
+ * below), to workgroups at the head of its grid, which take them once particle phase n has
+ * published its spread force; particle phase n+1 starts once those workgroups have stored step
+ * n+1's populations around its box.  The box may move by 2 nodes per step on either axis; a
+ * faster particle fails the simulation with LBIB_E_NUMERIC.  Every device-side wait is bounded:
+ * one that exceeds about a second fails the simulation with LBIB_E_NUMERIC.  Its two streams must
+ * run concurrently: a tool that serialises kernel dispatches (hardware-counter collection) makes
+ * those waits time out, so run mode 0 under it.  Serial (mode 0), always on the first step after
+ * lbib_init / lbib_load / lbib_write_particle, and where CU masking is unavailable or ny >= 2^23: the particle phase
  * and a sweep of all nodes run one after the other on the handle's stream.  The overlapped
  * schedule's sweep stream is CU-masked, which takes a hardware queue of its own: at most 8
  * simulations per device hold one at a time, and the others run the serial schedule until

@@ -201,7 +201,7 @@ int zone_workgroups(const Particle& p, bool pull)
 // widened box can reach, at most 64.
 int pair_zone_workgroups(const Particle& p, int rows)
 {
-    const int unit = 4 * kPairStrip, zs = p.zone_side;
+    const int unit = 4 * kPairStrip, zs = p.zone_side + 2 * (kPairZoneMargin - kZoneMargin);
     const int cols = (zs + unit - 2) / unit + 1, units = (zs + rows - 2) / rows + 1;
     return std::min(64, (cols * units * ((rows + 3) / 4) + 7) / 8 * 8);
 }

@@ -208,19 +208,20 @@ struct ParticleArgs {
     int32_t nparts;  // entries of refs
     // hand-over of the overlapped schedule (NULL: none): once its tile and desc have completed
     // the particle stores ready_value into the monotonic counter *ready; its prediction of the
-    // next box, widened, goes to the two words at zone_words, packed with zone_tag
+    // next box, widened by zone_margin, goes to the two words at zone_words, packed with zone_tag
     // (zone_pack), after its last read of f
     unsigned long long* ready;
     unsigned long long ready_value;
     unsigned long long* zone_words;
     uint32_t zone_tag;
+    int32_t zone_margin;  // kZoneMargin, or kPairZoneMargin where sweeps may take two steps
     // the particle launch of the overlapped schedule starts once *zdone reaches zdone_target
     // (the previous sweep's zone workgroups have stored their results; NULL: no wait), and
     // with check_prev checks that its box lies inside the box zone[parity_out] (the previous
     // step's), widened by kZoneMargin - 1
     // and in check_prev 2 (the first of two steps after another two swept together) that it lies
-    // so inside the box zone[2], that of the step before the previous one, which such a first
-    // step (pair_first) leaves there
+    // inside the box zone[2], that of the step before the previous one, which such a first
+    // step (pair_first) leaves there, widened by kPairZoneMargin - 1
     unsigned long long* zdone;
     unsigned long long zdone_target;
     int32_t check_prev;
@@ -251,9 +252,12 @@ hipError_t launch_init(T* f, int32_t nx, int32_t ny, int32_t pitch, int64_t plan
 // workgroup finishes.
 // The zone workgroups cover the box widened by kZoneMargin nodes and store coherently, then
 // count in at *zdone; the next particle launch waits for their count instead of the end of
-// the sweep, and reads the populations of its box, which lie in that widened box as long as
-// the box moves at most one node per step (the particle checks it).
+// the sweep, and reads the populations of its box, whose sources lie in that widened box as long
+// as the box moves at most two nodes per step (the particle checks it).  The units of a two-step
+// sweep cover the box of its first step widened by kPairZoneMargin, the same motion over two
+// steps.
 constexpr int kZoneMargin = 3;
+constexpr int kPairZoneMargin = 2 * (kZoneMargin - 1) + 1;
 struct HandoverArgs {
     const unsigned long long* zone_words;
     uint32_t zone_tag;
@@ -272,8 +276,8 @@ hipError_t launch_sweep_overlap(const T* fin, T* fout, const SweepArgs& a, const
 // Two steps (n, n+1) in one pass over memory (march_pair), beside the particle phase of one
 // particle, or of a lattice without particles (c.nzone 0).  A unit is four strips of kPairStrip
 // columns by `rows` rows, a workgroup each.  The first nzone workgroups take the units that
-// the box of step n reaches, widened by kZoneMargin nodes (as step n's zone words give it):
-// they first sweep step n at the nodes of that widened box into the other buffer,
+// the box of step n reaches, widened by kPairZoneMargin nodes (as step n's zone words give it):
+// they first sweep step n at the nodes of the box widened by kZoneMargin into the other buffer,
 // once the particle has published its force of step n, and count in at *zdone, which releases
 // the particle's step n+1; once its force is published too they run both steps of their units,
 // overwriting the zone, and count in again.  The other workgroups run the other units, which

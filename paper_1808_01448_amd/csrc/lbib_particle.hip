@@ -1356,7 +1356,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
             a.zone[a.parity_out] = z;
             // the next sweep reads the box from these words, and overwrites f once it has
             // them: f was last read by the probes, whose results the update above used
-            if (a.zone_words) zone_pack(widened(z, a.nx, a.ny, kZoneMargin), a.zone_tag, a.zone_words);
+            if (a.zone_words) zone_pack(widened(z, a.nx, a.ny, a.zone_margin), a.zone_tag, a.zone_words);
         }
     }
     return true;
@@ -1514,11 +1514,11 @@ __device__ __forceinline__ bool particle_phase(const ParticleArgs<T>& a, char* l
     c.box_ok = c.w > 0 && c.h > 0 && c.w <= a.nx && (int64_t)c.w * c.h <= a.box_cap;
     if (!c.box_ok && tid == 0) c.flags |= FLAG_TILE;
     if (MODE == 0 && a.zdone && a.check_prev && c.box_ok && tid == 0) {
-        // the previous sweep's zone workgroups covered the previous box (of the last two steps
-        // swept together, the first's) widened by kZoneMargin: this box must lie in it widened
-        // by kZoneMargin - 1 (its readers' sources one further)
+        // the previous sweep's zone workgroups covered the previous box widened by kZoneMargin
+        // (of the last two steps swept together, the first's widened by kPairZoneMargin): this
+        // box must lie in it widened by one node less (its readers' sources one further)
         const TileDesc zp = a.zone[a.check_prev == 2 ? 2 : a.parity_out];
-        const int m = kZoneMargin - 1;
+        const int m = (a.check_prev == 2 ? kPairZoneMargin : kZoneMargin) - 1;
         int dx = ((c.x0 - zp.i0w) % a.nx + a.nx) % a.nx;
         if (dx >= a.nx / 2) dx -= a.nx;
         const bool okx = zp.w + 2 * m >= a.nx || (dx >= -m && dx + c.w <= zp.w + m);

@@ -408,6 +408,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
             pa.ready_value = prev + 1;
             pa.zone_words = p.d_count + 2 + 2 * ((h->steps + 1) & 3);
             pa.zone_tag = (uint32_t)((prev + 1) & 0xffffu);
+            pa.zone_margin = h->pairs ? kPairZoneMargin : kZoneMargin;
             h->plaunches = prev + 1;
             // the overlapped schedule is the faster one at every size measured, from 256 x 64
             // (15.0 against 19.4 us per step: the sweep hides behind the particle phase) to
