@@ -753,6 +753,7 @@ struct PhaseCarry {
     int32_t valid;    // 1: all of it; 2: the pose alone (a helper)
     int32_t present;  // every helper of the run has started
     int32_t use;      // the helpers fill the next step's node fields
+    int32_t fits;     // this step's could come from helpers: they lie in LDS and fit HelpArea
 };
 
 // A step of a resident launch with helpers.  One CU draws the lines of a large particle's nodes
@@ -790,9 +791,9 @@ __device__ __forceinline__ uint32_t help_tag(const HelpStep& s, int32_t k, bool 
     return ((uint32_t)(s.base + (unsigned long long)k) << 1) | (use ? 1u : 0u);
 }
 // The leader's thread 0, with the pose of step s.next, for the helpers where this step's fields
-// were shared (fits).  The words carry their tag, so they need no order and no flag.  The pose
+// were shared (y.fits).  The words carry their tag, so they need no order and no flag.  The pose
 // after the run's last step, which nobody fills, ends the helpers.
-__device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, bool fits, double x, double yy, double th)
+__device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, double x, double yy, double th)
 {
     if (!y.present) {
         bool all = true;
@@ -801,7 +802,7 @@ __device__ __forceinline__ void help_send(const HelpStep& s, PhaseCarry& y, bool
             all &= (unsigned long long)coherent_load((const int64_t*)s.area->arrived + k) == s.base;
         y.present = all;
     }
-    const bool use = y.present && fits && s.next < s.nsteps;
+    const bool use = y.present && y.fits && s.next < s.nsteps;
     y.use = use;
     if (!use && s.next < s.nsteps) return;
     const unsigned long long tag = (unsigned long long)help_tag(s, s.next, use) << 32;
@@ -927,8 +928,7 @@ struct PhaseCtx {
     TileDesc zin;
     PhaseCarry* carry;
     HelpStep help;
-    bool shared;  // the step's node fields can come from helpers: they lie in LDS and fit HelpArea
-    bool helped;  // (the leader) and do
+    bool helped;  // (the leader) this step's node fields come from the helpers
 };
 
 // The phase runs on one CU, so it is bound by the latency of its chain for small particles and
@@ -1262,7 +1262,7 @@ __device__ __forceinline__ bool phase_body(const ParticleArgs<T>& a, const Phase
         if (!(isfinite(Fx) && isfinite(Fy) && isfinite(M) && isfinite(nux) && isfinite(nuy) && isfinite(nom)))
             fl |= FLAG_NONFINITE;
         if (kHelped<T> && MODE == 0 && c.carry && c.help.area)
-            help_send(c.help, *c.carry, c.shared, nxc, nyc, nth);
+            help_send(c.help, *c.carry, nxc, nyc, nth);
         // the state the next step starts from, stored coherently (as the bond flags)
         state_store(&st->xc1, xc);
         state_store(&st->yc1, yc);
@@ -1380,10 +1380,11 @@ __device__ __forceinline__ bool phase_rest(const ParticleArgs<T>& a, PhaseCtx<MP
     int* nodes = stride == 2 ? (int*)B.fx : (int*)(base + 5 * m);
     c.nodes = nodes;
     constexpr bool can_help = kHelped<T> && MODE == 0;  // (and a resident launch's: carry)
-    c.shared = LDS && m <= kHelpNodes;  // the leader's and the helpers' verdicts agree
+    const bool share = LDS && m <= kHelpNodes;  // the leader's and the helpers' verdicts agree
     // a helper of a step that is not shared is done: the global scratch is the leader's alone
-    if (can_help && c.carry && c.help.me != 0 && !c.shared) return true;
-    c.helped = can_help && c.carry && c.help.use && c.help.me == 0 && c.shared;
+    if (can_help && c.carry && c.help.me != 0 && !share) return true;
+    c.helped = can_help && c.carry && c.help.use && c.help.me == 0 && share;
+    if (can_help && c.carry && threadIdx.x == 0) c.carry->fits = share;  // (thread 0 reads it in help_send)
     if (c.helped) {
     } else if (c.whole) {
         if ((int)threadIdx.x < m) nodes[(int)threadIdx.x * stride] = (int)threadIdx.x;
