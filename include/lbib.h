@@ -253,8 +253,8 @@ lbib_status lbib_load(lbib_handle h, const void* blob, int64_t size);
  * leave it a sweep behind for the rest of the call.  On lattices whose sweep moves 16 MB or more
  * per step (and always there without particles) mode 2 sweeps two steps in one pass over memory,
  * a call's last odd step alone; the f - f_eq storages keep one step per sweep.  A call too short
- * to win back the hand-over between its streams (one step of any lattice, up to six of a small
- * one) runs serially in mode 2.  All schedules
+ * to win back the hand-over between its streams (up to four steps of a small lattice, one of most)
+ * runs serially in mode 2.  All schedules
  * give bit-identical results. */
 /* Several particles in one lattice: the particle phase is split in two halves over all
  * particles -- first every particle stages its box and spreads its marker forces, then every

@@ -257,6 +257,33 @@ int pair_rows(const LatticeGeom& g, bool particle)
     return particle || nodes >= (int64_t)1 << 23 ? 16 : nodes >= (int64_t)1 << 20 ? 8 : 4;
 }
 
+// Mode 2 runs a call too short to win its streams' hand-over back serially.  An overlapped step
+// hides the shorter of the sweep and the particle phase of nl markers (both estimated from the
+// serial launches), and the join of the two chains costs about 20 us once per call.  A single step
+// has it at 25 to 28 us, and its large particle's phase takes up to 1.6 times as long beside a
+// sweep that fills the memory, so there the sweep has to outlast twice what it hides.  us of a
+// call and a wait, serially / overlapped, by steps:
+//                                      1         2         3         4         6
+//   256 x 64 FP64, 64 markers       33/64     53/64     73/79     93/93   132/124
+//   1024 x 256 FP32, 192            38/56     62/74     87/89   111/110   159/144
+//   1024 x 400 FP16, 384            43/59     73/81   102/104   131/127   189/176
+//   2000 x 200 FP64, 320            47/61     80/83   115/108   148/127   215/168
+//   4096 x 1024 FP32, 64            73/81   133/105   193/142   252/176   371/245
+//   4096 x 1024 FP32, 960           98/110  178/151   260/208   342/250   506/352
+//   4096 x 1024 FP64, 576          138/129  262/179   384/289   509/320   757/460
+//   4096 x 1024 FP64, 960          147/131  278/191   408/312   544/336   806/480
+//   8192 x 4096 FP16, 960          251/250  484/351   713/582   952/668  1421/977
+//   2999 x 777 BF16 f - f_eq, 384   68/82   121/116   170/146   221/182   325/247
+//   2999 x 777 BF16 f - f_eq, 640   81/105  147/144   209/187   274/233   403/327
+bool short_call(const LatticeGeom& g, int nl, int64_t n)
+{
+    constexpr double kJoin = 20.0, kJoinAlone = 28.0;
+    const double sweep = 4.0 + (double)g.upd_bytes * g.nx * g.ny / 7e6;
+    const double phase = 14.5 + 0.031 * nl;
+    if (n == 1) return std::min(0.5 * sweep, phase) < kJoinAlone;
+    return (double)n * std::min(sweep, phase) < kJoin;
+}
+
 MarkedNodes marked_nodes(const Particle& p, int ny, double xc, double yc, double th)
 {
     struct Window {

@@ -130,6 +130,7 @@ int pair_zone_workgroups(const Particle& p, int rows);
 bool pair_sweeps(const LatticeGeom& g);
 bool pool_pair_sweeps(const std::vector<LatticeGeom>& members);
 int pair_rows(const LatticeGeom& g, bool particle);  // rows of a unit of the two-step sweep
+bool short_call(const LatticeGeom& g, int nl, int64_t n);  // mode 2 runs n steps serially
 // The nodes that the supports of the particle's markers and probes reach at a pose, and the nodes
 // of the box that holds them.
 struct MarkedNodes {

@@ -281,16 +281,6 @@ hipError_t ensure_sweep_stream(lbib_sim* h)
     return hipStreamCreateWithFlags(&h->stream3, hipStreamNonBlocking);
 }
 
-// Mode 2 runs a call too short to win its streams' hand-over back serially: each overlapped step
-// hides the shorter of the sweep and the particle phase (about 16 us), the call's join of the
-// two chains costs about 24 us (a step and a wait on 256 x 64 FP64: 34 us serially, 55 us
-// overlapped).
-bool short_call(const LatticeGeom& g, int64_t n)
-{
-    const double sweep_us = 3.0 + (double)g.upd_bytes * g.nx * g.ny / 6e6;
-    return (double)n * std::min(sweep_us, 16.0) < 24.0;
-}
-
 // One time step is the particle phase then the lattice sweep; mode 2 of a large lattice, and a
 // lattice without particles, sweep two steps in one pass over memory (PairHandover).  Serial schedule: both on the
 // caller's stream.  Overlapped schedule (when the previous step has predicted this step's
@@ -415,7 +405,7 @@ lbib_status enqueue_steps(lbib_sim* h, int64_t n)
             // 8192 x 4096 (the particle phase hides behind the sweep).  It needs the CU-masked
             // sweep stream: workgroups of the sweep and the particle's wait for each other on
             // the device, and the particle must always find a CU.
-            bool overlap = h->overlap == 1 || (h->overlap == 2 && !short_call(h->g, n));
+            bool overlap = h->overlap == 1 || (h->overlap == 2 && !short_call(h->g, p.nl, n));
             if (h->desc.ny >= (1 << 23)) overlap = false;  // the packed tiles (zone_pack)
             if (overlap && h->zone_valid) HIPCHK(h, ensure_sweep_stream(h));
             if (!h->masked) overlap = false;

@@ -38,6 +38,7 @@ int plan_particle(const lbib_lattice_desc* d, const lbib_particle_desc* pd, cons
     out[2] = particle_lds_slots(p.box_cap, (int32_t)m.box);
     return 0;
 }
+int plan_short(const lbib_lattice_desc* d, int nl, int64_t n) { return short_call(lattice_geom(*d), nl, n); }
 int plan_pool(const lbib_lattice_desc* d, int64_t n)
 {
     std::vector<LatticeGeom> g;
@@ -72,6 +73,10 @@ def lattice(nx, ny, precision):
     out = (C.c_int64 * 7)()
     shim().plan_lattice(C.byref(lattice_desc(nx, ny, precision)), out)
     return dict(zip(("interleaved", "pitch", "plane", "elem", "pairs", "rows_alone", "rows_particle"), out))
+
+
+def short_call(nx, ny, precision, nl, steps):
+    return bool(shim().plan_short(C.byref(lattice_desc(nx, ny, precision)), C.c_int(nl), C.c_int64(steps)))
 
 
 def pool_pairs(members):

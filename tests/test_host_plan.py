@@ -47,3 +47,26 @@ def test_population_planes_are_swept_step_by_step(prec):
     assert not g["interleaved"] and 3 * g["pitch"] * g["elem"] < 2**31
     assert not g["pairs"]
     assert not H.pool_pairs([(2048, 4096, prec), (238_609_408, 4, prec)])
+
+
+@pytest.mark.parametrize("nx,ny,prec,nl,serial,overlapped", [
+    # steps of a call that run faster one way, by 4 us or more
+    (256, 64, "fp64", 64, (1, 2, 3), (6, 7, 8, 100)),
+    (512, 128, "fp32", 128, (1, 2, 3), (6, 8)),
+    (1024, 256, "fp32", 192, (1, 2), (6, 8)),
+    (1024, 400, "fp16", 384, (1, 2), (4, 6, 8)),
+    (2000, 200, "fp64", 320, (1,), (3, 4, 6, 8)),
+    (2048, 600, "fp32", 576, (1,), (3, 4, 6, 8)),
+    (4096, 1024, "fp32", 64, (1,), (2, 3, 4, 6)),
+    (4096, 1024, "fp32", 256, (1,), (2, 3, 4, 6)),
+    (4096, 1024, "fp32", 960, (1,), (2, 3, 4, 6)),
+    (4096, 1024, "fp64", 576, (), (1, 2, 3, 4)),
+    (4096, 1024, "fp64", 960, (), (1, 2, 3, 4)),
+    (8192, 4096, "fp16", 960, (), (2, 3, 4)),
+    (2999, 777, "bf16_neq", 384, (1,), (2, 3, 4)),
+    (2999, 777, "bf16_neq", 640, (1,), (3, 4)),
+])
+def test_short_calls(nx, ny, prec, nl, serial, overlapped):
+    """The calls that mode 2 runs serially, by lattice, markers and steps."""
+    assert [H.short_call(nx, ny, prec, nl, n) for n in serial] == [True] * len(serial)
+    assert [H.short_call(nx, ny, prec, nl, n) for n in overlapped] == [False] * len(overlapped)
