@@ -199,7 +199,9 @@ lbib_status lbib_read_markers(lbib_handle h, int32_t pid, double* xy, double* nx
  *   which 1: u_x = (sum_q f_q e_qx + g_x / 2) / rho           [ny][nx]
  *   which 2: u_y likewise                                     [ny][nx]
  *   which 3: the populations f_q, plain FP64                  [9][ny][nx]
- * (the velocity excludes the immersed-boundary force of the coming step). */
+ * (the velocity excludes the immersed-boundary force of the coming step).  The GPU evaluates the
+ * field into a staging buffer as large as the result, at most 64 MiB, which the handle keeps from
+ * its first read on: in device memory, or in host memory where the device has no room. */
 lbib_status lbib_read_field(lbib_handle h, int32_t which, double* out, int64_t capacity);
 
 /* Overwrite the populations with plain FP64 values laid out [9][ny][nx] (count = 9 nx ny).

@@ -10,6 +10,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cstring>
 
 #include "lbib_device.hpp"
 #include "lbib_host.hpp"
@@ -84,28 +85,52 @@ constexpr size_t kStageMax = (size_t)64 << 20;
 
 }  // namespace
 
+void free_stage(FieldStage& st)
+{
+    if (st.p && st.host)
+        (void)hipHostFree(st.p);
+    else if (st.p)
+        (void)hipFree(st.p);
+    st = FieldStage{};
+}
+
+hipError_t reserve_stage(FieldStage& st, size_t want, size_t row_bytes, StageAlloc device, StageAlloc host)
+{
+    if (st.bytes >= want) return hipSuccess;
+    free_stage(st);
+    hipError_t e = hipSuccess;
+    // a smaller stage where the device has no room for a large one, down to one row
+    for (size_t bytes = want;; bytes = std::max(row_bytes, bytes / 2)) {
+        e = device((void**)&st.p, bytes);
+        if (e == hipSuccess) {
+            st.bytes = bytes;
+            return e;
+        }
+        st.p = nullptr;
+        (void)hipGetLastError();
+        if (e != hipErrorOutOfMemory) return e;
+        if (bytes <= row_bytes) break;
+    }
+    if ((e = host((void**)&st.p, want)) != hipSuccess) {
+        st.p = nullptr;
+        (void)hipGetLastError();
+        return e;
+    }
+    st.bytes = want;
+    st.host = true;
+    return hipSuccess;
+}
+
 hipError_t read_field(const void* f, const LatticeGeom& g, int which, double* out, FieldStage& st, hipStream_t s)
 {
     const SweepArgs a = make_sweep_args(g);
     const int64_t rows = (which == 3 ? 9 : 1) * (int64_t)g.ny;
     const size_t row_bytes = (size_t)g.nx * sizeof(double);
     const size_t want = std::min((size_t)rows * row_bytes, std::max(kStageMax, row_bytes));
-    hipError_t e = hipSuccess;
-    if (st.bytes < want) {
-        if (st.p) (void)hipFree(st.p);
-        st = FieldStage{};
-        size_t bytes = want;
-        // a smaller stage where the device has no room for a large one
-        while ((e = hipMalloc((void**)&st.p, bytes)) == hipErrorOutOfMemory && bytes > row_bytes) {
-            (void)hipGetLastError();
-            bytes = std::max(row_bytes, bytes / 2);
-        }
-        if (e != hipSuccess) {
-            st = FieldStage{};
-            return e;
-        }
-        st.bytes = bytes;
-    }
+    hipError_t e = reserve_stage(
+        st, want, row_bytes, [](void** p, size_t n) { return hipMalloc(p, n); },
+        [](void** p, size_t n) { return hipHostMalloc(p, n, hipHostMallocDefault); });
+    if (e != hipSuccess) return e;
     const int64_t most = std::min<int64_t>((int64_t)(st.bytes / row_bytes), 65535);  // rows of one launch's grid
     for (int64_t v = 0; v < rows; v += most) {
         const int64_t n = std::min(most, rows - v);
@@ -118,9 +143,11 @@ hipError_t read_field(const void* f, const LatticeGeom& g, int which, double* ou
             default: launch_field<bf16_neq_t>(f, a, g.pull, which, v, n, st.p, s); break;
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(out + (size_t)v * g.nx, st.p, (size_t)n * row_bytes, hipMemcpyDeviceToHost, s)) != hipSuccess)
+        if (!st.host && (e = hipMemcpyAsync(out + (size_t)v * g.nx, st.p, (size_t)n * row_bytes, hipMemcpyDeviceToHost,
+                                            s)) != hipSuccess)
             return e;
         if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+        if (st.host) std::memcpy(out + (size_t)v * g.nx, st.p, (size_t)n * row_bytes);
     }
     return hipSuccess;
 }

@@ -164,12 +164,19 @@ void set_null_error(const std::string& msg);
 // padding zeroed.
 hipError_t init_populations(void* f, const LatticeGeom& g, hipStream_t s);
 
-// Device staging of the field read-outs, kept by its simulation or pool: as large as the largest
-// result read, 64 MiB (or one row) at most.
+// Staging of the field read-outs, kept by its simulation or pool: as large as the largest result
+// read, 64 MiB (or one row) at most; in device memory, or where that has no room in pinned host
+// memory, which the GPU writes directly.
 struct FieldStage {
     double* p = nullptr;
     size_t bytes = 0;
+    bool host = false;
 };
+void free_stage(FieldStage& st);
+// Makes the stage hold `want` bytes, or at least row_bytes; device, host: its allocators
+// (hipMalloc and hipHostMalloc but in tests).
+using StageAlloc = hipError_t (*)(void** p, size_t bytes);
+hipError_t reserve_stage(FieldStage& st, size_t want, size_t row_bytes, StageAlloc device, StageAlloc host);
 // rho (which 0), u_x (1), u_y (2) or the plain populations [9][ny][nx] (3) of a device buffer,
 // in FP64, to the caller's memory; enqueued on `s` and waited for.
 hipError_t read_field(const void* f, const LatticeGeom& g, int which, double* out, FieldStage& st, hipStream_t s);

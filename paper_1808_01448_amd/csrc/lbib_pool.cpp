@@ -912,7 +912,7 @@ void lbib_pool_destroy(lbib_pool_handle h)
     dfree(h->d_ptable);
     dfree(h->d_tile_b);
     dfree(h->d_ctl);
-    dfree(h->stage.p);
+    free_stage(h->stage);
     if (h->graph) (void)hipGraphExecDestroy(h->graph);
     for (int k = 0; k < 2; ++k)
         for (auto e : h->ev[k]) (void)hipEventDestroy(e);

@@ -165,8 +165,7 @@ void free_all(lbib_sim* h)
     dfree(h->d_items);
     if (h->ev_end) (void)hipEventDestroy(h->ev_end);
     h->ev_end = nullptr;
-    dfree(h->stage.p);
-    h->stage.bytes = 0;
+    free_stage(h->stage);
     dfree(h->d_pair);
     dfree(h->d_help);
     h->pairs = false;

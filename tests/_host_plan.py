@@ -6,6 +6,8 @@ import os
 import subprocess
 import tempfile
 
+import numpy as np
+
 from paper_1808_01448_amd import build, lbib
 
 SHIM = r"""
@@ -37,6 +39,49 @@ int plan_particle(const lbib_lattice_desc* d, const lbib_particle_desc* pd, cons
     out[1] = m.nodes;
     out[2] = particle_lds_slots(p.box_cap, (int32_t)m.box);
     return 0;
+}
+// the stage that a read-out of `want` bytes in rows of `row` gets where the device can give `room`
+// bytes at most and the host gives any (host_ok) or none
+static int64_t room;
+static int host_ok;
+int plan_stage(int64_t r, int ok, int64_t want, int64_t row, int64_t* out)
+{
+    room = r;
+    host_ok = ok;
+    FieldStage st;
+    const hipError_t e = reserve_stage(
+        st, (size_t)want, (size_t)row,
+        [](void** p, size_t n) {
+            if ((int64_t)n > room) return hipErrorOutOfMemory;
+            *p = (void*)0x1000;
+            return hipSuccess;
+        },
+        [](void** p, size_t) {
+            if (!host_ok) return hipErrorOutOfMemory;
+            *p = (void*)0x2000;
+            return hipSuccess;
+        });
+    out[0] = (int64_t)st.bytes;
+    out[1] = st.host;
+    out[2] = st.p == (double*)0x1000 ? 1 : st.p == (double*)0x2000 ? 2 : st.p == nullptr ? 0 : -1;
+    return (int)e;
+}
+// field `which` of a lattice's initial state, through a stage in device or in host memory
+int field_through(const lbib_lattice_desc* d, int which, int host, double* out)
+{
+    const LatticeGeom g = lattice_geom(*d);
+    void* f = nullptr;
+    FieldStage st;
+    st.bytes = (which == 3 ? 9 : 1) * (size_t)g.nx * g.ny * sizeof(double);
+    st.host = host != 0;
+    hipError_t e = hipMalloc(&f, g.buf_bytes);
+    if (e == hipSuccess)
+        e = host ? hipHostMalloc((void**)&st.p, st.bytes, hipHostMallocDefault) : hipMalloc((void**)&st.p, st.bytes);
+    if (e == hipSuccess) e = init_populations(f, g, nullptr);
+    if (e == hipSuccess) e = read_field(f, g, which, out, st, nullptr);
+    free_stage(st);
+    (void)hipFree(f);
+    return (int)e;
 }
 int plan_short(const lbib_lattice_desc* d, int nl, int64_t n) { return short_call(lattice_geom(*d), nl, n); }
 int plan_pool(const lbib_lattice_desc* d, int64_t n)
@@ -77,6 +122,19 @@ def lattice(nx, ny, precision):
 
 def short_call(nx, ny, precision, nl, steps):
     return bool(shim().plan_short(C.byref(lattice_desc(nx, ny, precision)), C.c_int(nl), C.c_int64(steps)))
+
+
+def stage(room, host_ok, want, row):
+    out = (C.c_int64 * 3)()
+    e = shim().plan_stage(C.c_int64(room), C.c_int(host_ok), C.c_int64(want), C.c_int64(row), out)
+    return e, out[0], bool(out[1]), ("none", "device", "host")[out[2]]
+
+
+def field_through(nx, ny, precision, which, host):
+    out = np.zeros((9 if which == 3 else 1, ny, nx))
+    d = lattice_desc(nx, ny, precision, drive=1)
+    assert shim().field_through(C.byref(d), which, int(host), out.ctypes.data_as(C.POINTER(C.c_double))) == 0
+    return out
 
 
 def pool_pairs(members):
