@@ -103,7 +103,10 @@ struct BoxForce {
 // resource's bound drops), so the compiler knows how many younger accesses are in flight when
 // it waits for a row's loads and does not wait for those.  Row-interleaved buffers only (R = 9 P):
 // the window's three pitches then hold all nine populations of its three rows.
-constexpr uint32_t kNoStore = 0xC0000000u;  // beyond every bound (the window's bytes are below 2^31)
+// beyond every bound (the window's bytes are below 2^31, and so is a segment's offset, which the
+// sum of the two does not carry past 32 bits)
+constexpr uint32_t kNoStore = 0x80000000u;
+static_assert((uint64_t)kNoStore + 0x7fffffffu <= 0xffffffffu && kNoStore > 0x7fffffffu, "dropped at every segment");
 
 template <typename S>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_window(const S* f, const SweepArgs& a, int j)
