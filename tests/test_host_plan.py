@@ -70,3 +70,24 @@ def test_short_calls(nx, ny, prec, nl, serial, overlapped):
     """The calls that mode 2 runs serially, by lattice, markers and steps."""
     assert [H.short_call(nx, ny, prec, nl, n) for n in serial] == [True] * len(serial)
     assert [H.short_call(nx, ny, prec, nl, n) for n in overlapped] == [False] * len(overlapped)
+
+
+def test_the_pair_tests_sweep_pairs():
+    """The lattices and calls of the GPU tests of the two-step sweeps take that path."""
+    import test_gpu_pairs as P
+    import test_gpu_pool_pairs as Q
+
+    for (nx, ny), prec in itertools.product(P.SIZES + [(1024, 260)], ("fp64", "fp32", "fp16", "bf16")):
+        if (nx, ny) == (1024, 260) and prec in ("fp16", "bf16"):
+            continue  # used with the wider storages
+        assert H.lattice(nx, ny, prec)["pairs"], (nx, ny, prec)
+        for q in P.PARTICLES.values():
+            long = [n for n in P.CALLS if not H.short_call(nx, ny, prec, q.get("nl", 64), n)]
+            assert any(n % 2 for n in long) and any(n % 2 == 0 for n in long), (nx, ny, prec, long)
+    for prec, nx, ny in next(m for m in P.test_fluid_alone.pytestmark if m.args[:1] == ("prec,nx,ny",)).args[1]:
+        assert H.lattice(nx, ny, prec)["pairs"], (nx, ny, prec)
+    for prec in ("fp64", "fp32", "fp16", "bf16"):
+        f = Q.filler(prec)["lattice"]
+        assert H.pool_pairs([(nx, ny, prec) for nx, ny in Q.EDGES] + [(f["nx"], f["ny"], prec)])
+        assert H.pool_pairs([(64, 32, prec), (f["nx"], f["ny"], prec)])
+    assert not H.lattice(256, 64, "fp64")["pairs"] and not H.pool_pairs([(256, 64, "fp64")] * 12)
