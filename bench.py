@@ -30,9 +30,14 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 METRIC = "aggregate MLUPS & % HBM roofline; batched/served vs plain; p50/p99 solve latency"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_sweep_4096x1024_fp32.json")
 TRAFFIC_FILE_BEYOND = os.path.join(ROOT, "profiles", "traffic_sweep_8192x4096_storages.json")
-# the lattice sweep's device code: the counters in the traffic files are valid for these sources only
-KERNEL_SRCS = [os.path.join(ROOT, "paper_1808_01448_amd", "csrc", f)
-               for f in ("lbib_sweep.hip", "lbib_march.hpp", "lbib_collide.hpp", "lbib_device.hpp")]
+# the lattice sweep's device code: the counters in the traffic files are valid for these sources
+# only, and for the rule of the two-step sweep's units (pair_rows)
+CSRC = os.path.join(ROOT, "paper_1808_01448_amd", "csrc")
+KERNEL_SRCS = [os.path.join(CSRC, f) for f in ("lbib_sweep.hip", "lbib_march.hpp", "lbib_collide.hpp",
+                                               "lbib_device.hpp", "lbib_internal.hpp")]
+# rows of a unit of the timed two-step sweeps, which run beside a particle: the counted ones must
+# have as many, since a unit reads two rows more than it updates
+ROWS_PER_UNIT = 16
 LEGS = ("beyond", "c1", "batched", "multi", "serve", "cpu")
 
 
@@ -44,7 +49,15 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in KERNEL_SRCS:
         h.update(open(f, "rb").read())
+    host = open(os.path.join(CSRC, "lbib_host.cpp")).read()
+    rule = host.index("int pair_rows(")
+    h.update(host[rule:host.index("\n}\n", rule)].encode())
     return h.hexdigest()[:16]
+
+
+def counts_apply(entry: dict) -> bool:
+    """Whether a counted launch has the shape of the timed one."""
+    return entry.get("steps_per_launch") != 2 or entry.get("rows_per_unit") == ROWS_PER_UNIT
 
 
 def measured_traffic(cells: int) -> dict:
@@ -55,7 +68,7 @@ def measured_traffic(cells: int) -> dict:
         t = json.load(open(TRAFFIC_FILE))
     except (OSError, ValueError):
         return none
-    if t.get("kernel_source_sha256_16") != kernel_source_hash() or t.get("cells") != cells:
+    if t.get("kernel_source_sha256_16") != kernel_source_hash() or t.get("cells") != cells or not counts_apply(t):
         return none
     return {"traffic": t.get("hbm_bytes_per_launch"), "traffic_kernel": t.get("kernel")}
 
@@ -72,7 +85,7 @@ def measured_traffic_beyond(storage: str, cells: int) -> dict:
     if t.get("kernel_source_sha256_16") != kernel_source_hash():
         return none
     for e in t.get("entries", []):
-        if e.get("storage") == storage and e.get("cells") == cells:
+        if e.get("storage") == storage and e.get("cells") == cells and counts_apply(e):
             return {"traffic": e.get("hbm_bytes_per_launch"), "traffic_kernel": e.get("kernel")}
     return none
 

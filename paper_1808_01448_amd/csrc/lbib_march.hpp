@@ -10,10 +10,11 @@
 // per node and step is that of the one-step sweeps in the same order on the same values, so
 // results are bit-identical.
 //
-// What bounds it: memory still (the vector units are about half busy), through the lines that
-// neighbouring strips share and the two extra rows of a run.  No particle, us per step, one-step
-// sweep against this one: 8192 x 4096 FP64 900 -> 530, FP32 417 -> 275, FP16 215 -> 176;
-// 4096 x 1024 FP64 92 -> 65, FP32 43.2 -> 34.  Without the barrier that keeps a workgroup's
+// What bounds it: FP64 and FP32, memory still (vector issue about 0.2 and 0.5 of the cycles), through
+// the lines that neighbouring strips share and the two extra rows of a run; the 16-bit storages,
+// vector issue (0.8).  No particle, us per step, one-step sweep against this one: 8192 x 4096
+// FP64 867 -> 546, FP32 380 -> 273, FP16 189 -> 142; 4096 x 1024 FP64 88 -> 62, FP32 43 -> 32.6,
+// FP16 23.8 -> 18.8.  Without the barrier that keeps a workgroup's
 // strips on the same rows, 370 instead of 275 (FP32, 8192 x 4096); with loads past the caches
 // 343; with each wave on 64 aligned columns and its neighbours' values missing (no usable
 // result) 290, so the shared lines are what the barrier saves.
